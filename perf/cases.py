@@ -298,3 +298,65 @@ def tolerance(case):
     if case["kind"] == "combine":       # float32 sums; the final O is rounded to bf16, where the last bit may go either way
         return {"rel": 2e-5, "max": 1e-4} if case["dtype"] == "f32" else {"rel": 2e-3, "max": 0.02}
     return {"rel": 1e-5, "max": 1e-4} if case.get("dtype") == "f32" else {"rel": 1e-2, "max": 0.6}
+
+
+# ---- the same in 64 bits ------------------------------------------------------------------------
+
+def _exact_attention(case, s):
+    """Masked softmax attention and its gradients by their definition, one head and a few hundred query rows at a time."""
+    hq, hkv, d, f64 = case["hq"], case["hkv"], case.get("d", 128), torch.float64
+    q_rows = s["q"].shape[0]
+    if case["kind"] == "ring":
+        n, c, rank = case["n"], case["c"], case["rank"]
+        chunk = torch.arange(c, device=DEV)
+        k_pos = torch.cat([chunk + ch * c for r in range(n) for ch in (r, 2 * n - 1 - r)])
+        q_pos = torch.cat([chunk + ch * c for ch in (rank, 2 * n - 1 - rank)])
+    else:
+        n_k = s["k"].shape[0]
+        k_pos, q_pos = torch.arange(n_k, device=DEV), torch.arange(n_k - q_rows, n_k, device=DEV)
+    order = torch.argsort(k_pos)                            # key rows in sequence order: position p is row order[p]
+    first = torch.zeros_like(q_pos)
+    if "cu" in s:
+        cu = s["cu"].long()
+        first = cu[torch.searchsorted(cu, q_pos, right=True) - 1]
+    scale = 1.0 / math.sqrt(d)
+    o = torch.empty(q_rows, hq, d, dtype=f64, device=DEV)
+    lse = torch.empty(hq, q_rows, dtype=f64, device=DEV)
+    if case["backward"]:
+        dq, dk, dv = torch.empty_like(o), torch.zeros(len(order), hkv, d, dtype=f64, device=DEV), torch.zeros(len(order), hkv, d, dtype=f64, device=DEV)
+    pos = torch.arange(len(order), device=DEV)
+    for kv in range(hkv):
+        k = s["k"].reshape(-1, hkv, d)[order, kv].to(f64)
+        v = s["v"].reshape(-1, hkv, d)[order, kv].to(f64)
+        for r0 in range(0, q_rows, 512):
+            rows = slice(r0, min(r0 + 512, q_rows))
+            lo, hi = int(first[rows].min()), int(q_pos[rows].max()) + 1
+            hidden = (pos[lo:hi] > q_pos[rows, None]) | (pos[lo:hi] < first[rows, None])
+            for h in range(kv * (hq // hkv), (kv + 1) * (hq // hkv)):
+                q = s["q"][rows, h].to(f64)
+                p = (q @ k[lo:hi].T).mul_(scale).masked_fill_(hidden, -math.inf)
+                lse[h, rows] = torch.logsumexp(p, 1)
+                p.sub_(lse[h, rows, None]).exp_()
+                o[rows, h] = p @ v[lo:hi]
+                if case["backward"]:
+                    do = s["do"][rows, h].to(f64)
+                    dv[lo:hi, kv] += p.T @ do
+                    ds = (do @ v[lo:hi].T).sub_((do * o[rows, h]).sum(1, keepdim=True)).mul_(p).mul_(scale)
+                    dq[rows, h] = ds @ k[lo:hi]
+                    dk[lo:hi, kv] += ds.T @ q
+    if not case["backward"]:
+        return o, lse
+    back = torch.argsort(order)
+    return o, lse, dq, dk[back].reshape(s["k"].shape), dv[back].reshape(s["k"].shape)
+
+
+def exact(case, seed):
+    if case["kind"] == "move":
+        return None
+    s = prepare(case, seed)
+    if case["kind"] != "combine":
+        return _exact_attention(case, s)
+    (o1, l1), (o2, l2) = [(o.double(), lse.double()) for o, lse in s["parts"]]
+    lse = torch.logaddexp(l1, l2)
+    o = torch.exp(l1 - lse).T[:, :, None] * o1 + torch.exp(l2 - lse).T[:, :, None] * o2
+    return o, lse, o, (o * s["do"].double()).sum(2).T.contiguous()
