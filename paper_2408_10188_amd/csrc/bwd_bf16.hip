@@ -13,7 +13,7 @@
 // Each recomputes S and dP (7 tile products in total instead of 5) in exchange for
 // exclusive ownership of its outputs.
 //
-// Workspace of a backward call (dK/dV kernel only): [-LSE*log2e | delta] padded to whole
+// Workspace of a backward call (dK/dV kernel only): [-LSE*log2e | -delta] padded to whole
 // 64-row tiles, then the area for partial dK / dV sums of split key tiles.
 #include "common.h"
 
@@ -22,26 +22,26 @@ namespace {
 
 __global__ __launch_bounds__(256) void bwd_stats_kernel(const float* __restrict__ lse, const float* __restrict__ delta,
                                                         int64_t lse_hs, int row0, int n_rows, int padded,
-                                                        float* __restrict__ nl2, float* __restrict__ dl) {
+                                                        float* __restrict__ nl2, float* __restrict__ ndl) {
   const int i = blockIdx.x * 256 + threadIdx.x, h = blockIdx.y;
   if (i >= padded) return;
-  float n = -INFINITY, d = 0.f;
+  float n = -INFINITY, nd = 0.f;
   if (i < n_rows) {
     const float L = lse[(int64_t)h * lse_hs + row0 + i];
     n = L == -INFINITY ? -INFINITY : -L * kLog2e;      // a row that saw nothing: P = exp2(-inf) = 0
-    d = delta[(int64_t)h * lse_hs + row0 + i];
+    nd = -delta[(int64_t)h * lse_hs + row0 + i];
   }
   nl2[(int64_t)h * padded + i] = n;
-  dl[(int64_t)h * padded + i] = d;
+  ndl[(int64_t)h * padded + i] = nd;
 }
 
 }  // namespace
 
 hipError_t launch_bwd_stats(const float* lse, const float* delta, int64_t lse_hs, int Hq, int row0, int n_rows,
-                            float* nl2, float* dl, hipStream_t stream) {
+                            float* nl2, float* ndl, hipStream_t stream) {
   const int padded = (int)tiles_of(n_rows) * 64;
   if (padded == 0) return hipSuccess;
-  bwd_stats_kernel<<<dim3((padded + 255) / 256, Hq), dim3(256), 0, stream>>>(lse, delta, lse_hs, row0, n_rows, padded, nl2, dl);
+  bwd_stats_kernel<<<dim3((padded + 255) / 256, Hq), dim3(256), 0, stream>>>(lse, delta, lse_hs, row0, n_rows, padded, nl2, ndl);
   return hipGetLastError();
 }
 
@@ -55,9 +55,9 @@ hipError_t bwd_bf16_prepare(const StepArgs& a, BwdWorkspace& w, hipStream_t stre
   const int64_t t = tiles_of(a.n_q);
   char* p = a.ws;
   float* nl2 = reinterpret_cast<float*>(p);  p += a.Hq * t * 64 * sizeof(float);
-  float* dl = reinterpret_cast<float*>(p);   p += a.Hq * t * 64 * sizeof(float);
-  w.nl2 = nl2; w.dl = dl; w.partial = reinterpret_cast<float*>(p); w.n_qtiles = (int32_t)t;
-  return launch_bwd_stats(a.lse_final, a.delta, a.lse_hs, a.Hq, a.q_row0, a.n_q, nl2, dl, stream);
+  float* ndl = reinterpret_cast<float*>(p);   p += a.Hq * t * 64 * sizeof(float);
+  w.nl2 = nl2; w.ndl = ndl; w.partial = reinterpret_cast<float*>(p); w.n_qtiles = (int32_t)t;
+  return launch_bwd_stats(a.lse_final, a.delta, a.lse_hs, a.Hq, a.q_row0, a.n_q, nl2, ndl, stream);
 }
 
 hipError_t launch_bwd_bf16(const StepArgs& a, hipStream_t stream) {

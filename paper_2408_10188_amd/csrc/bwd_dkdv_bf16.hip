@@ -35,6 +35,25 @@ constexpr int kDepth = 4;                        // LDS operand reads in flight 
 #define MMSP_PIN_ACC(x) asm volatile("" : "+a"(x))     // keeps an accumulator in the AGPR half of the register file
 #define MMSP_STEP_END() __builtin_amdgcn_sched_barrier(0)
 
+// The first products (S, dP) as inline assembly: their results are consumed by vector
+// instructions, so they belong in the VGPR half of the register file, but the compiler puts every
+// accumulator of a function that uses AGPRs into AGPRs and then copies the 64 results of a tile
+// back one v_accvgpr_read each.  Of the 518 instructions of a tile those copies and the 32
+// subtractions of delta (now the accumulator's start value) were 96.  The compiler does not know
+// that these are matrix instructions, so the waits it would insert are the caller's:
+//  * A comes straight from an LDS read and B (AGPRs) never changes: no vector instruction writes
+//    an operand shortly before;
+//  * a result may be read by a vector instruction only behind four more matrix instructions
+//    (each holds the issue of the next for its eight passes; nineteen wait states are required), or behind
+//    MMSP_RESULT_WAIT: MMSP_PIN of the result at that place keeps earlier readers out.
+__device__ __forceinline__ void mfma32_v_first(f32x16& d, const u32x4& a, const u32x4& b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(b));
+}
+__device__ __forceinline__ void mfma32_v(f32x16& d, const u32x4& a, const u32x4& b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(b));
+}
+#define MMSP_RESULT_WAIT(x) asm volatile("s_nop 15\n\ts_nop 7" : "+v"(x))
+
 // kMask = false: the host has checked that every (query, key) pair of the block is visible and
 // that n_q is a multiple of the tile length, so no tile needs masking.
 // nsplit > 1: the (query tile, head) sequence of every key tile is dealt out to nsplit
@@ -58,7 +77,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
   char* const os1 = os0 + kTileBytes;
   char* const os2 = os1 + kTileBytes;
   char* const os3 = os2 + kTileBytes;
-  float* const st0 = reinterpret_cast<float*>(lds + kStRegion);   // [0,64) -LSE*log2e, [64,128) delta
+  float* const st0 = reinterpret_cast<float*>(lds + kStRegion);   // [0,64) -LSE*log2e, [64,128) -delta
   float* const st1 = st0 + 128;
   float* const st2 = st1 + 128;
   float* const st3 = st2 + 128;
@@ -127,7 +146,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
       vreg[ks] = *reinterpret_cast<const u32x4*>(pv + ks * 16);
     }
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) { MMSP_PIN(kreg[ks]); MMSP_PIN(vreg[ks]); }   // landed before the tile copies are counted
+    for (int ks = 0; ks < 8; ++ks) { MMSP_PIN_ACC(kreg[ks]); MMSP_PIN_ACC(vreg[ks]); }   // landed before the tile copies are counted; AGPRs
   }
   const float c = a.scale * kLog2e;
 
@@ -144,7 +163,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
     const int64_t q_tile_bytes = (int64_t)kBQ * a.q_ts * 2, do_tile_bytes = (int64_t)kBQ * a.Hq * 256;
     const int64_t q_head_bytes = (int64_t)a.q_hs * 2;
     const int64_t st_head_bytes = (int64_t)w.n_qtiles * kBQ * 4;
-    const char* stat_src = reinterpret_cast<const char*>((wave_s & 1) ? w.dl : w.nl2) + (int64_t)kvh * a.group * st_head_bytes;
+    const char* stat_src = reinterpret_cast<const char*>((wave_s & 1) ? w.ndl : w.nl2) + (int64_t)kvh * a.group * st_head_bytes;
     const DmaOffs<kCopies> qoff_full = dma_s_offsets<kCopies>(a.q_ts, kBQ, wave, lane);
     const DmaOffs<kCopies> dooff_full = dma_s_offsets<kCopies>((int64_t)a.Hq * 128, kBQ, wave, lane);
     // the last query tile of the block may be ragged: rows past the end repeat the last row
@@ -167,7 +186,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
     auto fetch_begin = [&]() {
       Fetch f;
       f.q = f_q; f.d_o = f_do; f.st = f_st;
-      f.ragged = f_qt == qt_ragged;
+      f.ragged = kMask && f_qt == qt_ragged;              // without a mask n_q is a multiple of the tile
       if (f_it + 1 < niter) {                           // past the end the last tile is fetched again (into a free slot)
         ++f_it;
         f_hg += nsplit; f_q += step_q; f_do += step_do; f_st += step_st;
@@ -183,7 +202,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
         const int p = piece - kCopies;
         dma16(f.d_o, f.ragged ? dooff_ragged.o[p] : dooff_full.o[p], odst, (wave_s + p * W) * 1024);
       } else {
-        dma4(f.st, (uint32_t)lane * 4, sdst, (wave_s & 1) * 256);   // even wavefronts fetch -LSE*log2e, odd ones delta
+        dma4(f.st, (uint32_t)lane * 4, sdst, (wave_s & 1) * 256);   // even wavefronts fetch -LSE*log2e, odd ones -delta
       }
     };
     auto fetch = [&](char* qdst, char* odst, float* sdst) {
@@ -226,8 +245,8 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
     int c_hg = split % a.group, c_qt = qt1 - split / a.group;
 
     // Software pipeline state carried from block to block.
-    f32x16 s_nx, dp_nx;          // S and dP of the next block (first products, being accumulated)
-    f32x16 p_cur, dp_cur;        // P (fp32) and dP of the current block
+    f32x16 s_nx, dp_nx;          // S and dP - delta of the next block (first products, being accumulated)
+    f32x16 p_cur, dp_cur;        // P (fp32) and dP - delta of the current block
     u32x4 pb0, pb1;              // P of the current block packed as B operands (rows 0..15, 16..31)
     u32x4 oq[kDepth];            // LDS operands in flight, kDepth matrix instructions deep
 
@@ -265,19 +284,30 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
         x[i] = (qrow < rlo || qrow > rhi) ? -INFINITY : x[i];
       }
     };
+    // start value of dP's accumulator: -delta of the block's rows, read from LDS into its registers
+    auto load_ndl = [&](f32x16& x, const float* slot, int row0) {
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const float4 d = stat4(slot, 64 + row0 + g4 * 8);
+        x[g4 * 4 + 0] = d.x; x[g4 * 4 + 1] = d.y; x[g4 * 4 + 2] = d.z; x[g4 * 4 + 3] = d.w;
+      }
+    };
     auto needs_mask = [&](int q0) { return kMask && (q0 < w_lo_max || q0 + 31 > w_hi_min); };
 
     // ---- prologue: S, dP and P of the first block ----
     __builtin_amdgcn_s_waitcnt(0x0F70 | ((2 * kGroup) & 15) | (((2 * kGroup) >> 4) << 14));   // vmcnt(2 kGroup): the first tile has landed (two newer groups may be in flight)
     lds_barrier();
     {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) { s_nx[i] = 0.f; dp_nx[i] = 0.f; }
+      load_ndl(dp_nx, st0, 0);
 #pragma unroll
       for (int ks = 0; ks < 8; ++ks) {
-        s_nx = mfma32(*reinterpret_cast<const u32x4*>(qs0 + na[ks]), kreg[ks], s_nx);
-        dp_nx = mfma32(*reinterpret_cast<const u32x4*>(os0 + na[ks]), vreg[ks], dp_nx);
+        const u32x4 oq_ = *reinterpret_cast<const u32x4*>(qs0 + na[ks]), oo_ = *reinterpret_cast<const u32x4*>(os0 + na[ks]);
+        if (ks == 0) mfma32_v_first(s_nx, oq_, kreg[ks]);
+        else mfma32_v(s_nx, oq_, kreg[ks]);
+        mfma32_v(dp_nx, oo_, vreg[ks]);
       }
+      MMSP_RESULT_WAIT(s_nx);
+      MMSP_RESULT_WAIT(dp_nx);
       if (needs_mask(c_qt * kBQ)) apply_mask(s_nx, c_qt * kBQ);
       uint32_t pw[8];
 #pragma unroll
@@ -293,6 +323,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
       pb0 = mk4(pw[0], pw[1], pw[2], pw[3]);
       pb1 = mk4(pw[4], pw[5], pw[6], pw[7]);
       dp_cur = dp_nx;
+      load_ndl(dp_nx, st0, 32);
     }
 
     // One tile: four phases of 16 matrix instructions.  cq / co / cs: this tile's slot, nq / no / ns:
@@ -318,36 +349,32 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
       for (int ph = 0; ph < 4; ++ph) {
         const int blk = ph >> 1;                         // block of this tile the phase works for
         if ((ph & 1) == 0) {
-          // ---- phase A: S, dP of the following block beside dS of block blk ----
-          float4 dl[4];
-#pragma unroll
-          for (int g4 = 0; g4 < 4; ++g4) dl[g4] = stat4(cs, 64 + blk * 32 + g4 * 8);
-#pragma unroll
-          for (int i = 0; i < 16; ++i) { s_nx[i] = 0.f; dp_nx[i] = 0.f; }
+          // ---- phase A: S, dP - delta of the following block beside dS of block blk ----
           uint32_t sw[8];
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
             const int n = ph * 16 + i, ks = i >> 1;
             u32x4 op = oq[n & (kDepth - 1)];
             MMSP_PIN(op);
-            if ((i & 1) == 0) s_nx = mfma32(op, kreg[ks], s_nx);
-            else dp_nx = mfma32(op, vreg[ks], dp_nx);
+            if (i == 0) mfma32_v_first(s_nx, op, kreg[0]);
+            else if ((i & 1) == 0) mfma32_v(s_nx, op, kreg[ks]);
+            else mfma32_v(dp_nx, op, vreg[ks]);
             oq[n & (kDepth - 1)] = operand(n + kDepth, cq, co, nq, no);
             if (n % 7 == 3 && n / 7 < kGroup) fetch_piece(fx, n / 7, rq, ro, rs);
             if (i >= 4 && i < 12) {                      // dS of rows 2j, 2j+1 of the lane's 16 (one pair per step)
               const int j = i - 4, e = 2 * j;
-              const float d0 = (e & 3) == 0 ? dl[e >> 2].x : dl[e >> 2].z;
-              const float d1 = (e & 3) == 0 ? dl[e >> 2].y : dl[e >> 2].w;
-              sw[j] = pack2(p_cur[e] * (dp_cur[e] - d0), p_cur[e + 1] * (dp_cur[e + 1] - d1));
+              sw[j] = pack2(p_cur[e] * dp_cur[e], p_cur[e + 1] * dp_cur[e + 1]);
               MMSP_PIN(sw[j]);
             }
-            if ((i & 1) == 0) MMSP_PIN_ACC(s_nx); else MMSP_PIN_ACC(dp_nx);
             MMSP_STEP_END();
           }
           // hand over: the packed dS of block blk feeds phase B; S / dP of the following block become current
           const u32x4 ds0 = mk4(sw[0], sw[1], sw[2], sw[3]), ds1 = mk4(sw[4], sw[5], sw[6], sw[7]);
           const int q0_f = blk == 0 ? q0 + 32 : q0_next;  // first row of the following block
-          if (needs_mask(q0_f)) apply_mask(s_nx, q0_f);
+          if (needs_mask(q0_f)) {
+            MMSP_RESULT_WAIT(s_nx);
+            apply_mask(s_nx, q0_f);
+          }
           MMSP_STEP_END();
           // ---- phase B: dV, dK of block blk beside P of the following block ----
           const float* fs = blk == 0 ? cs + 32 : ns;     // -LSE*log2e of the following block's rows
@@ -355,7 +382,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
 #pragma unroll
           for (int g4 = 0; g4 < 4; ++g4) nl[g4] = stat4(fs, g4 * 8);
           uint32_t pw[8];
-          f32x16 p_nx;
+          f32x16 p_nx, dp_ld;
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
             const int n = (ph + 1) * 16 + i, tq = i >> 3, db = (i >> 1) & 3;
@@ -365,6 +392,8 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
             else dk[db] = mfma32(op, tq ? ds1 : ds0, dk[db]);
             oq[n & (kDepth - 1)] = operand(n + kDepth, cq, co, nq, no);
             if (n % 7 == 3 && n / 7 < kGroup) fetch_piece(fx, n / 7, rq, ro, rs);
+            if (i == 4) { MMSP_PIN(s_nx); MMSP_PIN(dp_nx); }   // four matrix instructions behind the last first product
+            if (i == 12) load_ndl(dp_ld, ns, blk * 32);  // for the block after the following one
             if (i >= 4 && i < 12) {                      // P of rows 2j, 2j+1
               const int j = i - 4, e = 2 * j;
               const float n0 = (e & 3) == 0 ? nl[e >> 2].x : nl[e >> 2].z;
@@ -381,6 +410,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
           pb1 = mk4(pw[4], pw[5], pw[6], pw[7]);
           p_cur = p_nx;
           dp_cur = dp_nx;
+          dp_nx = dp_ld;
           MMSP_STEP_END();
         }
       }

@@ -34,7 +34,7 @@ struct StepArgs {
 // Workspace views of one backward call (all inside the caller's workspace).
 struct BwdWorkspace {
   const float* nl2;    // -LSE*log2e, [Hq][n_qtiles*64], -inf where LSE = -inf and in the padding
-  const float* dl;     // delta,      [Hq][n_qtiles*64], 0 in the padding
+  const float* ndl;    // -delta,     [Hq][n_qtiles*64], 0 in the padding
   float* partial;      // partial dK then dV of split key tiles, bwd_dkdv_partial_bytes() in all
   int32_t n_qtiles;
 };
@@ -92,9 +92,9 @@ hipError_t launch_merge(float* o_acc, float* lse_acc, const float* o_part, const
 hipError_t launch_delta(const void* o_final, const void* d_o, float* delta, int io_dtype,
                         int64_t lse_hs, int Hq, int d, int row0, int n_rows, hipStream_t stream);
 
-// Padded per-row statistics of the backward: nl2 = -LSE*log2e (or -inf), dl = delta.
+// Padded per-row statistics of the backward: nl2 = -LSE*log2e (or -inf), ndl = -delta.
 hipError_t launch_bwd_stats(const float* lse, const float* delta, int64_t lse_hs, int Hq, int row0, int n_rows,
-                            float* nl2, float* dl, hipStream_t stream);
+                            float* nl2, float* ndl, hipStream_t stream);
 hipError_t launch_bwd_dkdv_bf16(const StepArgs& a, const BwdWorkspace& w, hipStream_t stream);
 int64_t bwd_bf16_workspace_bytes(int Hq, int64_t n_q);
 int64_t bwd_dkdv_partial_bytes();
