@@ -14,8 +14,8 @@
 // only about 8: up to five or six ordinary vector instructions fit beside it if they are
 // independent and interleaved in program order.  The loop is therefore software-pipelined inside
 // every wavefront: while the matrix pipe works on P.V of tile t-1 the vector units take the
-// maximum and the first half of the exponentials of tile t, and while it works on S of tile t+1
-// they take the second half.  The interleaving is written out step by step (one matrix
+// first half of the exponentials of tile t, and while it works on S of tile t+1 they take the
+// second half.  The interleaving is written out step by step (one matrix
 // instruction per step) and pinned with empty asm statements and scheduling barriers.
 // Tiles wholly outside every row's visible key interval are skipped; only tiles that cut an
 // interval boundary (the causal diagonal, a document start) pay for masking.
@@ -139,10 +139,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
   for (int db = 0; db < 4; ++db)
 #pragma unroll
     for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
-  // Softmax state.  m_ref is the raw-score reference the exponentials are taken against; it
-  // follows the running row maximum lazily: it only moves when the maximum has grown by more
-  // than kLazy in the exponent (P stays <= 2^kLazy), so the O rescale is rare.
+  // Softmax state.  m_ref is the raw-score reference the exponentials are taken against.  It
+  // is the maximum of the first tile the row sees and moves only when a later tile's sum shows that
+  // its maximum has grown by more than kLazy in the exponent, so the steady loop takes no maxima
+  // (30 of its 150 vector instructions a tile did) and its exponentials need not wait for one.
   constexpr float kLazy = 8.f;
+  constexpr float kSumLimit = 32.f * 256.f;              // 32 keys per lane and tile, 2^kLazy each
   float m_ref = -INFINITY;
   float neg_mc = 0.f;        // -m_ref * c  (0 while m_ref = -inf, so masked scores give exp2(-inf) = 0)
   float l = 0.f;             // this lane's share of the row sum (its 32 of every 64 keys)
@@ -217,13 +219,10 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
 #define MMSP_PIN(x) asm volatile("" : "+v"(x))
 #define MMSP_STEP_END() __builtin_amdgcn_sched_barrier(0)
 
-    // ================= phase 1: O^T += V(t-1)^T P(t-1)^T  beside  max(t) and the first exponentials of tile t =================
+    // ================= phase 1: O^T += V(t-1)^T P(t-1)^T  beside the first half of the exponentials of tile t =================
     // (the first iteration multiplies an all-zero P with a slot of zeros)
-    float alpha = 1.f;
-    bool moved = false;
     uint32_t w[16];          // P^T of tile t, two keys per word
     float ps[4] = {0.f, 0.f, 0.f, 0.f};                 // fp32 sums of the unrounded P (LSE needs 1e-3)
-    float mx = -INFINITY, mx_other = -INFINITY;
     auto exp_item = [&](int j) {                        // keys 2j, 2j+1 of the lane's 32
       const f32x16& sv = s[j >> 3];
       const int e = (j & 7) * 2;
@@ -251,44 +250,16 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
           vq[i & 3][0] = lds_read_tr(vt + va[db][0] + (g + 1) * 4096);
           vq[i & 3][1] = lds_read_tr(vt + va[db][1] + (g + 1) * 4096);
         }
-        if (i < 5) {                                    // running maximum: 32 scores in 16 three-input maxima
-          const f32x16& sv = s[i >= 3 ? 1 : 0];
-          if (i == 0) { mx = fmaxf(fmaxf(sv[0], sv[1]), sv[2]); mx = fmaxf(fmaxf(mx, sv[3]), sv[4]); mx = fmaxf(fmaxf(mx, sv[5]), sv[6]); }
-          if (i == 1) { mx = fmaxf(fmaxf(mx, sv[7]), sv[8]); mx = fmaxf(fmaxf(mx, sv[9]), sv[10]); mx = fmaxf(fmaxf(mx, sv[11]), sv[12]); }
-          if (i == 2) { mx = fmaxf(fmaxf(mx, sv[13]), sv[14]); mx = fmaxf(fmaxf(mx, sv[15]), s[1][0]); mx = fmaxf(fmaxf(mx, s[1][1]), s[1][2]); }
-          if (i == 3) { mx = fmaxf(fmaxf(mx, sv[3]), sv[4]); mx = fmaxf(fmaxf(mx, sv[5]), sv[6]); mx = fmaxf(fmaxf(mx, sv[7]), sv[8]); }
-          if (i == 4) { mx = fmaxf(fmaxf(mx, sv[9]), sv[10]); mx = fmaxf(fmaxf(mx, sv[11]), sv[12]); mx = fmaxf(fmaxf(mx, sv[13]), sv[14]);
-                        mx = fmaxf(mx, sv[15]); mx_other = __shfl_xor(mx, 32); }
-          MMSP_PIN(mx);
-        }
-        if (i == 6) {                                   // lazily followed reference (branch-free; only the O rescale is conditional)
-          mx = fmaxf(mx, mx_other);
-          moved = mx > m_ref + lazy_raw;
-          const float m_new = moved ? mx : m_ref;
-          alpha = moved ? __builtin_amdgcn_exp2f((m_ref - m_new) * c) : 1.f;   // m_ref = -inf -> 0
-          m_ref = m_new;
-          neg_mc = m_new == -INFINITY ? 0.f : -m_new * c;
-          l *= alpha;
-          MMSP_PIN(neg_mc); MMSP_PIN(alpha); MMSP_PIN(l);
-        }
-        if (i >= 8) {                                   // exponentials of keys 0..15 of the lane
-          exp_item(i - 8);
-        }
+        if (i & 1) exp_item(i >> 1);                    // exponentials of keys 0..15 of the lane
         MMSP_PIN(oacc[db]);
         MMSP_STEP_END();
       }
     }
-    if (__any(moved)) {                                 // rare after the first tiles
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[db][i] *= alpha;
-    }
-    MMSP_STEP_END();
 
     // ================= phase 2: S^T of tile t+1  beside  the remaining exponentials of tile t =================
     // (after the last tile the product runs on whatever the slot holds and is never used)
     f32x16 sn[2];
+    float tile_sum;          // this lane's share of the tile's row sum
     {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
@@ -303,12 +274,42 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
         const int ks = i >> 1, kb = i & 1;
         sn[kb] = mfma32(kq[i & 3], qreg[ks], sn[kb]);
         if (i + 4 < 16) kq[i & 3] = *reinterpret_cast<const u32x4*>(ktile - kKRegion + ka[ks + 2] + kb * 8192);
-        if (i < 8) exp_item(8 + i);
+        if ((i & 1) == 0) exp_item(8 + (i >> 1));
         MMSP_PIN(sn[kb]);
         MMSP_STEP_END();
       }
-      l += (ps[0] + ps[1]) + (ps[2] + ps[3]);
+      tile_sum = (ps[0] + ps[1]) + (ps[2] + ps[3]);
     }
+    MMSP_STEP_END();
+    // ---- the reference (rare: the first tile a row sees, later ones whose maximum outgrew it) ----
+    // A score above m_ref by more than kLazy in the exponent shows in the lane's sum of 32 terms:
+    // while the sum is below 32 * 2^kLazy no P exceeds that, so neither P (bf16 has float's range)
+    // nor the sums lose anything, and the maximum itself is never needed.  Otherwise the reference
+    // moves to the tile's maximum and the tile's exponentials, whose scores are still here, are
+    // taken again.  Both lanes of a row (its two halves of the keys) decide alike.
+    if (__any(tile_sum > kSumLimit || m_ref == -INFINITY)) {
+      float mx = -INFINITY;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kb][i]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const bool moved = mx > m_ref + lazy_raw;
+      const float m_new = moved ? mx : m_ref;
+      const float alpha = moved ? __builtin_amdgcn_exp2f((m_ref - m_new) * c) : 1.f;   // m_ref = -inf -> 0
+      m_ref = m_new;
+      neg_mc = m_new == -INFINITY ? 0.f : -m_new * c;
+      l *= alpha;
+#pragma unroll
+      for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[db][i] *= alpha;
+      ps[0] = ps[1] = ps[2] = ps[3] = 0.f;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) exp_item(j);
+      tile_sum = (ps[0] + ps[1]) + (ps[2] + ps[3]);
+    }
+    l += tile_sum;
     MMSP_STEP_END();
 #pragma unroll
     for (int g = 0; g < 4; ++g) pb[g] = mk4(w[4 * g], w[4 * g + 1], w[4 * g + 2], w[4 * g + 3]);
