@@ -78,16 +78,24 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
   key_interval_of_row(a, tile_row0, t_lo, dummy);
   key_interval_of_row(a, min(tile_row0 + kBM, a.n_q) - 1, dummy, t_hi);
   int w_lo_max, w_hi_min;                               // wavefront: largest lo, smallest hi
+  int w_lo_min, w_hi_max;
   {
     const int wr0 = min(tile_row0 + wave * 32, a.n_q - 1), wr1 = min(tile_row0 + wave * 32 + 31, a.n_q - 1);
-    key_interval_of_row(a, wr0, dummy, w_hi_min);
-    key_interval_of_row(a, wr1, w_lo_max, dummy);
+    key_interval_of_row(a, wr0, w_lo_min, w_hi_min);
+    key_interval_of_row(a, wr1, w_lo_max, w_hi_max);
   }
   int kt0 = t_lo / kBN, kt1 = t_hi >= t_lo ? t_hi / kBN : kt0 - 1;   // inclusive tile range
   kt0 = __builtin_amdgcn_readfirstlane(kt0);
   kt1 = __builtin_amdgcn_readfirstlane(kt1);
   w_lo_max = __builtin_amdgcn_readfirstlane(w_lo_max);
   w_hi_min = __builtin_amdgcn_readfirstlane(w_hi_min);
+  w_lo_min = __builtin_amdgcn_readfirstlane(w_lo_min);
+  w_hi_max = __builtin_amdgcn_readfirstlane(w_hi_max);
+  // Iterations this wavefront has work in: from the one that computes S of its first tile to the one
+  // that multiplies P of its last.  Outside them it only helps to move tiles, which leaves the SIMD
+  // to the wavefront it shares it with (a causal diagonal of 256 rows, documents shorter than that).
+  const bool w_any = w_lo_min <= w_hi_max;
+  const int t_first = w_any ? w_lo_min / kBN - 1 : 1 << 30, t_last = w_any ? w_hi_max / kBN + 1 : -1;
 
   // ---- asynchronous tile fetch ----
   const char* kbase = reinterpret_cast<const char*>(a.k) + ((int64_t)a.k_row0 * a.kv_ts + (int64_t)kvh * a.kv_hs) * 2;
@@ -199,6 +207,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
     lds_barrier();
     fetch(kc, kbase, k_refill);
     fetch(vc, vbase, v_refill);
+    if (t < t_first || t > t_last) return;
 
     const int k0 = t * kBN;
     // ---- mask (only tiles that cut an interval boundary) ----
@@ -287,7 +296,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
     // nor the sums lose anything, and the maximum itself is never needed.  Otherwise the reference
     // moves to the tile's maximum and the tile's exponentials, whose scores are still here, are
     // taken again.  Both lanes of a row (its two halves of the keys) decide alike.
-    if (__any(tile_sum > kSumLimit || m_ref == -INFINITY)) {
+    if (__any(tile_sum > kSumLimit || (m_ref == -INFINITY && lo < k0 + kBN && hi >= k0))) {
       float mx = -INFINITY;
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
