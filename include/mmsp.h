@@ -176,10 +176,11 @@ mmsp_status mmsp_a2a_pack_heads(int64_t n_tokens, int32_t U, int64_t slice_bytes
 mmsp_status mmsp_a2a_unpack_heads(int64_t n_tokens, int32_t U, int64_t slice_bytes, const void* y, void* x, void* hip_stream);
 
 /* Bytes of device workspace the step calls need for blocks of at most n_q_max x n_k_max rows.
- * The forward needs none (0; its kernels read the caller's tensors in place), neither does
- * f32.  The bf16 backward (`backward` != 0) uses the workspace for the block's row statistics
+ * The forward needs none (0; its kernels read the caller's tensors in place, but see there),
+ * neither does f32.  The bf16 backward (`backward` != 0) uses the workspace for the block's row statistics
  * (-LSE and delta, padded to whole tiles: 8 bytes per query row and head) and for partial
- * dK/dV sums of key tiles whose query range was cut into several workgroups (a fixed 64 MiB);
+ * dK/dV sums of key tiles, or partial dQ of query tiles, whose work was cut into several
+ * workgroups (a fixed 64 MiB);
  * nothing in it outlives the kernels of a call.  The workspace must be 16-byte aligned; a call
  * given less returns MMSP_ERR_WORKSPACE_TOO_SMALL.  Two calls that may overlap in time
  * (different streams) need separate workspaces. */
@@ -194,7 +195,9 @@ size_t mmsp_workspace_bytes(const mmsp_shape* shape, int64_t n_q_max, int64_t n_
  *   partial is applied in the kernel's epilogue (same arithmetic as mmsp_attn_merge).
  * Rows outside [q_row0, q_row0+n_q) are not touched.  A row that sees nothing gets
  * O_part = 0, LSE_part = -inf (and leaves a running result unchanged).
- * workspace: at least mmsp_workspace_bytes(shape, n_q, n_k, 0) bytes (may be NULL when 0). */
+ * workspace: at least mmsp_workspace_bytes(shape, n_q, n_k, 0) bytes (may be NULL when 0).  Given
+ *   more (the backward's size is plenty), a bf16 block with too few query rows to fill the GPU has its
+ *   keys shared out to several workgroups, whose partial results use up to 64 MiB of it. */
 mmsp_status mmsp_attn_step_fwd(const mmsp_shape* shape, const mmsp_block* blk,
                                const void* q, const void* k, const void* v,
                                float* o, float* lse, int accumulate,

@@ -298,7 +298,7 @@ mmsp_status mmsp_attn_step_fwd(const mmsp_shape* shape, const mmsp_block* blk, c
   }
   mmsp::StepArgs a = make_args(shape, blk);
   a.q = q; a.k = k; a.v = v; a.o = o; a.lse = lse; a.accumulate = accumulate != 0;
-  a.ws = reinterpret_cast<char*>(workspace);
+  if (workspace != nullptr && aligned16(workspace)) { a.ws = reinterpret_cast<char*>(workspace); a.ws_bytes = (int64_t)workspace_bytes; }
   if (shape->io_dtype == MMSP_BF16) return device_result(mmsp::launch_fwd_bf16(a, stream), "step_fwd (bf16)");
   return device_result(mmsp::launch_fwd_f32(a, stream), "step_fwd (f32)");
 }
@@ -406,6 +406,7 @@ mmsp_status mmsp_attn_step_bwd(const mmsp_shape* shape, const mmsp_block* blk, c
   }
   mmsp::StepArgs a = make_args(shape, blk);
   a.ws = reinterpret_cast<char*>(workspace);
+  a.ws_bytes = (int64_t)workspace_bytes;
   a.q = q; a.k = k; a.v = v; a.d_o = d_o; a.lse_final = lse_final; a.delta = delta;
   a.dq = dq_acc; a.dk = dk; a.dv = dv; a.accumulate = accumulate_dkdv != 0;
   if (shape->io_dtype == MMSP_BF16) return device_result(mmsp::launch_bwd_bf16(a, stream), "step_bwd (bf16)");

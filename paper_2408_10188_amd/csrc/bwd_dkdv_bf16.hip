@@ -504,13 +504,7 @@ hipError_t launch_bwd_dkdv_bf16(const StepArgs& a, const BwdWorkspace& w, hipStr
   const int n_kt = (a.n_k + kKeys - 1) / kKeys;
   // One workgroup per (key tile, KV head) fills the chip only if there are about as many as
   // CUs; with fewer, cut every key tile's query sequence into ranges.
-  static int cu_of_device[64] = {};                     // 0 = not asked yet; the count never changes for a device
-  int dev = 0, n_cu = 0;
-  if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) n_cu = cu_of_device[dev];
-  if (n_cu == 0) {
-    if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0) n_cu = kSplitMaxBlocks / 2;
-    if (dev >= 0 && dev < 64) cu_of_device[dev] = n_cu;
-  }
+  const int n_cu = cu_count();
   // With every pair visible all key tiles carry the same work and one round of workgroups is
   // best; under a mask the work per key tile varies (by 2x across a causal block), so aim for
   // two rounds of shorter workgroups, which the dispatcher then balances (heavy tiles come first).

@@ -21,7 +21,10 @@ constexpr int kBM = 32 * kWaves;   // query rows per workgroup
 constexpr int kBN = 64;            // keys per tile
 constexpr int kCopies = 16 / kWaves;
 
-__global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_qt, int xcd_per_kv) {
+// kPartial: nsplit workgroups share the key tiles of every query tile, each stores its share of dQ in
+// part [nsplit][n_q][Hq][128] for launch_dq_combine.
+template <bool kPartial>
+__global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_qt, int xcd_per_kv, int nsplit, float* part) {
   // LDS map: the three K slots in [0, 48 KiB), the three V slots in [48 KiB, 96 KiB); slots are
   // selected at compile time (the loop is unrolled three tiles deep).  An LDS instruction's
   // immediate offset reaches 64 KiB, so the V reads go through per-lane base registers that
@@ -41,18 +44,20 @@ __global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a,
 
   // workgroup -> (head, query tile): the workgroups of a KV head share an XCD, later (heavier
   // under the causal mask) query tiles first
-  int h, qt;
+  int h, qt, split = 0;
+  const int n_items = kPartial ? n_qt * nsplit : n_qt;   // per head
   if (xcd_per_kv > 0) {
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int kvh0 = xcd / xcd_per_kv;
     const int item = slot * xcd_per_kv + (xcd % xcd_per_kv);
-    if (item >= a.group * n_qt) return;
+    if (item >= a.group * n_items) return;
     h = kvh0 * a.group + item % a.group;
-    qt = n_qt - 1 - item / a.group;
+    qt = n_items - 1 - item / a.group;
   } else {
     h = blockIdx.x % a.Hq;
-    qt = n_qt - 1 - blockIdx.x / a.Hq;
+    qt = n_items - 1 - blockIdx.x / a.Hq;
   }
+  if (kPartial) { split = qt % nsplit; qt /= nsplit; }
   const int kvh = h / a.group;
   const int tile_row0 = qt * kBM;
   const int row = tile_row0 + wave * 32 + col;          // block-relative query row of this lane
@@ -74,6 +79,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a,
   int kt0 = t_lo / kBN, kt1 = t_hi >= t_lo ? t_hi / kBN : kt0 - 1;   // inclusive tile range
   kt0 = __builtin_amdgcn_readfirstlane(kt0);
   kt1 = __builtin_amdgcn_readfirstlane(kt1);
+  if (kPartial) {                                              // this workgroup's share of the tiles
+    const int total = max(kt1 - kt0 + 1, 0), first = kt0;
+    kt0 = first + (int)((int64_t)total * split / nsplit);
+    kt1 = first + (int)((int64_t)total * (split + 1) / nsplit) - 1;
+  }
   w_lo_max = __builtin_amdgcn_readfirstlane(w_lo_max);
   w_hi_min = __builtin_amdgcn_readfirstlane(w_hi_min);
   w_lo_min = __builtin_amdgcn_readfirstlane(w_lo_min);
@@ -230,13 +240,13 @@ __global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a,
   __builtin_amdgcn_s_waitcnt(0x0F70);                    // drain the copies issued past the end
 
   if (!live) return;
-  float* out = a.dq + ((int64_t)(a.q_row0 + row) * a.Hq + h) * 128 + half * 4;
+  float* out = (kPartial ? part + ((int64_t)split * a.n_q + row) * a.Hq * 128 : a.dq + (int64_t)(a.q_row0 + row) * a.Hq * 128) + h * 128 + half * 4;
 #pragma unroll
   for (int db = 0; db < 4; ++db)
 #pragma unroll
     for (int g4 = 0; g4 < 4; ++g4) {
       float4* dst = reinterpret_cast<float4*>(out + db * 32 + g4 * 8);
-      float4 o = *dst;
+      float4 o = kPartial ? make_float4(0.f, 0.f, 0.f, 0.f) : *dst;
       o.x += a.scale * dq[db][g4 * 4 + 0]; o.y += a.scale * dq[db][g4 * 4 + 1];
       o.z += a.scale * dq[db][g4 * 4 + 2]; o.w += a.scale * dq[db][g4 * 4 + 3];
       *dst = o;
@@ -247,12 +257,21 @@ __global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a,
 
 hipError_t launch_bwd_dq_bf16(const StepArgs& a, hipStream_t stream) {
   const int n_qt = (a.n_q + kBM - 1) / kBM;
-  int xcd_per_kv = 0, n_blocks = n_qt * a.Hq;
+  // the partial results lie where the dK/dV kernel, later on the same stream, keeps its own
+  const int64_t stats = bwd_bf16_workspace_bytes(a.Hq, a.n_q) - bwd_dkdv_partial_bytes();
+  const int nsplit = pick_key_ranges(a, n_qt * a.Hq, (int64_t)a.n_q * a.Hq * 128 * sizeof(float), a.ws_bytes - stats);
+  int xcd_per_kv = 0, n_blocks = n_qt * nsplit * a.Hq;
   if (8 % a.Hkv == 0) {
     xcd_per_kv = 8 / a.Hkv;
-    n_blocks = 8 * ((a.group * n_qt + xcd_per_kv - 1) / xcd_per_kv);
+    n_blocks = 8 * ((a.group * n_qt * nsplit + xcd_per_kv - 1) / xcd_per_kv);
   }
-  bwd_dq_bf16_kernel<<<dim3(n_blocks), dim3(64 * kWaves), 0, stream>>>(a, n_qt, xcd_per_kv);
+  if (nsplit > 1) {
+    float* part = reinterpret_cast<float*>(a.ws + stats);
+    bwd_dq_bf16_kernel<true><<<dim3(n_blocks), dim3(64 * kWaves), 0, stream>>>(a, n_qt, xcd_per_kv, nsplit, part);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_dq_combine(a, part, nsplit, stream);
+  }
+  bwd_dq_bf16_kernel<false><<<dim3(n_blocks), dim3(64 * kWaves), 0, stream>>>(a, n_qt, xcd_per_kv, 1, nullptr);
   return hipGetLastError();
 }
 

@@ -28,7 +28,8 @@ struct StepArgs {
   int32_t mask;                 // 0 full, 1 causal-diag
   int32_t n_docs;
   int32_t accumulate;           // fwd: merge into running state; bwd: add to dk/dv
-  char* ws;                     // caller's workspace (bf16 backward)
+  char* ws;                     // caller's workspace (bf16; nullptr or too small for a cut: no cut)
+  int64_t ws_bytes;
 };
 
 // Workspace views of one backward call (all inside the caller's workspace).
@@ -95,6 +96,13 @@ hipError_t launch_delta(const void* o_final, const void* d_o, float* delta, int 
 // Padded per-row statistics of the backward: nl2 = -LSE*log2e (or -inf), ndl = -delta.
 hipError_t launch_bwd_stats(const float* lse, const float* delta, int64_t lse_hs, int Hq, int row0, int n_rows,
                             float* nl2, float* ndl, hipStream_t stream);
+
+// Query tiles whose key range is cut into several workgroups (forward, dQ), see split.hip.
+int cu_count();
+int pick_key_ranges(const StepArgs& a, int n_blocks, int64_t bytes_per_range, int64_t room);
+hipError_t launch_fwd_combine(const StepArgs& a, const float* part_o, const float* part_lse, int nsplit, hipStream_t stream);
+hipError_t launch_dq_combine(const StepArgs& a, const float* part, int nsplit, hipStream_t stream);
+
 hipError_t launch_bwd_dkdv_bf16(const StepArgs& a, const BwdWorkspace& w, hipStream_t stream);
 int64_t bwd_bf16_workspace_bytes(int Hq, int64_t n_q);
 int64_t bwd_dkdv_partial_bytes();

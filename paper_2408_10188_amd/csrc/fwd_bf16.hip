@@ -30,8 +30,13 @@ constexpr int kBN = 64;            // keys per tile
 constexpr int kCopies = 16 / kWaves;
 constexpr int kSlots = 3;
 
-template <bool kAccum>
-__global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, int n_qt, int xcd_per_kv) {
+enum Result { kStore, kMerge, kPartial };
+
+// kPartial: nsplit workgroups share the key tiles of every query tile, each stores its (O, LSE) in
+// part_o [nsplit][n_q][Hq][128] and part_lse [nsplit][Hq][n_q] for launch_fwd_combine.
+template <Result kResult>
+__global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, int n_qt, int xcd_per_kv, int nsplit, float* part_o,
+                                                                  float* part_lse) {
   // Tile j (counted from the first visible tile) lives in slot j % 3 of its ring; slots are
   // selected at compile time (the loop is unrolled three tiles deep).  LDS map: the three V slots
   // in [0, 48 KiB), the three K slots in [48 KiB, 96 KiB).  An LDS instruction's immediate offset
@@ -53,18 +58,20 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
   // Workgroup -> (head, query tile).  Workgroups are dealt round-robin to the 8 XCDs; the
   // ones that land on the same XCD work on the same KV head so its K/V block stays in that
   // XCD's L2.  Later (heavier under the causal mask) query tiles go first.
-  int h, qt;
+  int h, qt, split = 0;
+  const int n_items = kResult == kPartial ? n_qt * nsplit : n_qt;   // per head
   if (xcd_per_kv > 0) {
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int kvh0 = xcd / xcd_per_kv;
     const int item = slot * xcd_per_kv + (xcd % xcd_per_kv);
-    if (item >= a.group * n_qt) return;
+    if (item >= a.group * n_items) return;
     h = kvh0 * a.group + item % a.group;
-    qt = n_qt - 1 - item / a.group;
+    qt = n_items - 1 - item / a.group;
   } else {
     h = blockIdx.x % a.Hq;
-    qt = n_qt - 1 - blockIdx.x / a.Hq;
+    qt = n_items - 1 - blockIdx.x / a.Hq;
   }
+  if (kResult == kPartial) { split = qt % nsplit; qt /= nsplit; }
   const int kvh = h / a.group;
   const int tile_row0 = qt * kBM;
   const int row = tile_row0 + wave * 32 + col;          // block-relative query row of this lane
@@ -87,6 +94,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
   int kt0 = t_lo / kBN, kt1 = t_hi >= t_lo ? t_hi / kBN : kt0 - 1;   // inclusive tile range
   kt0 = __builtin_amdgcn_readfirstlane(kt0);
   kt1 = __builtin_amdgcn_readfirstlane(kt1);
+  if (kResult == kPartial) {                                              // this workgroup's share of the tiles
+    const int total = max(kt1 - kt0 + 1, 0), first = kt0;
+    kt0 = first + (int)((int64_t)total * split / nsplit);
+    kt1 = first + (int)((int64_t)total * (split + 1) / nsplit) - 1;
+  }
   w_lo_max = __builtin_amdgcn_readfirstlane(w_lo_max);
   w_hi_min = __builtin_amdgcn_readfirstlane(w_hi_min);
   w_lo_min = __builtin_amdgcn_readfirstlane(w_lo_min);
@@ -366,10 +378,10 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
   const float lse_part = empty ? -INFINITY : (m * c + __builtin_amdgcn_logf(l)) * kLn2;   // v_log_f32 is log2
   if (!live) return;
   const int64_t r = a.q_row0 + row;
-  float* op = a.o + (r * a.Hq + h) * 128 + half * 4;
-  float* lp = a.lse + (int64_t)h * a.lse_hs + r;
+  float* op = (kResult == kPartial ? part_o + ((int64_t)split * a.n_q + row) * a.Hq * 128 : a.o + r * a.Hq * 128) + h * 128 + half * 4;
+  float* lp = kResult == kPartial ? part_lse + ((int64_t)split * a.Hq + h) * a.n_q + row : a.lse + (int64_t)h * a.lse_hs + r;
   float wa = 0.f, wb = inv;
-  if (kAccum) {
+  if (kResult == kMerge) {
     const float la = *lp;
     const float mm = fmaxf(la, lse_part);
     if (mm == -INFINITY) return;                        // both sides empty
@@ -388,7 +400,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
       float4* dst = reinterpret_cast<float4*>(op + db * 32 + g4 * 8);
       float4 o = make_float4(oacc[db][g4 * 4 + 0] * wb, oacc[db][g4 * 4 + 1] * wb, oacc[db][g4 * 4 + 2] * wb,
                              oacc[db][g4 * 4 + 3] * wb);
-      if (kAccum) {
+      if (kResult == kMerge) {
         const float4 old = *dst;
         o.x += wa * old.x; o.y += wa * old.y; o.z += wa * old.z; o.w += wa * old.w;
       }
@@ -400,14 +412,22 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
 
 hipError_t launch_fwd_bf16(const StepArgs& a, hipStream_t stream) {
   const int n_qt = (a.n_q + kBM - 1) / kBM;
-  int xcd_per_kv = 0, n_blocks = n_qt * a.Hq;
+  const int nsplit = pick_key_ranges(a, n_qt * a.Hq, (int64_t)a.n_q * a.Hq * 129 * sizeof(float), a.ws_bytes);
+  int xcd_per_kv = 0, n_blocks = n_qt * nsplit * a.Hq;
   if (8 % a.Hkv == 0) {
     xcd_per_kv = 8 / a.Hkv;
-    n_blocks = 8 * ((a.group * n_qt + xcd_per_kv - 1) / xcd_per_kv);
+    n_blocks = 8 * ((a.group * n_qt * nsplit + xcd_per_kv - 1) / xcd_per_kv);
   }
   const dim3 g(n_blocks), b(64 * kWaves);
-  if (a.accumulate) fwd_bf16_kernel<true><<<g, b, 0, stream>>>(a, n_qt, xcd_per_kv);
-  else fwd_bf16_kernel<false><<<g, b, 0, stream>>>(a, n_qt, xcd_per_kv);
+  if (nsplit > 1) {
+    float* part_o = reinterpret_cast<float*>(a.ws);
+    float* part_lse = part_o + (int64_t)nsplit * a.n_q * a.Hq * 128;
+    fwd_bf16_kernel<kPartial><<<g, b, 0, stream>>>(a, n_qt, xcd_per_kv, nsplit, part_o, part_lse);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_fwd_combine(a, part_o, part_lse, nsplit, stream);
+  }
+  if (a.accumulate) fwd_bf16_kernel<kMerge><<<g, b, 0, stream>>>(a, n_qt, xcd_per_kv, 1, nullptr, nullptr);
+  else fwd_bf16_kernel<kStore><<<g, b, 0, stream>>>(a, n_qt, xcd_per_kv, 1, nullptr, nullptr);
   return hipGetLastError();
 }
 

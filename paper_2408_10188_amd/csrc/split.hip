@@ -1,0 +1,125 @@
+// Cutting the key range of query-stationary kernels (forward, dQ) into several workgroups per query tile,
+// and the kernels that combine the partial results.
+//
+// A workgroup owns 256 query rows of one head and fills a CU by itself, so a block of few rows leaves
+// most of the chip idle for as long as one workgroup needs for all keys: 203 rows x 28 heads are 28
+// workgroups on 256 CUs, 720 us for 32768 keys.  With the keys cut in nine ranges, each storing
+// its partial result in the caller's workspace, the same step takes about 130 us.
+#include <algorithm>
+
+#include "common.h"
+
+namespace mmsp {
+namespace {
+
+// (O, LSE) of a row = log-sum-exp merge of its partial results, and with the running one when accumulate.  One
+// thread per 4 elements of d; the 32 threads of a (row, head) lie in one wavefront, whose lanes have
+// all read the running LSE before lane 0 of the 32 replaces it.
+__global__ __launch_bounds__(256) void fwd_combine_kernel(const float* __restrict__ part_o, const float* __restrict__ part_lse, int nsplit,
+                                                          int n_q, int Hq, int row0, float* __restrict__ o, float* __restrict__ lse,
+                                                          int64_t lse_hs, bool accumulate) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t rh = t >> 5;
+  if (rh >= (int64_t)n_q * Hq) return;
+  const int h = (int)(rh % Hq);
+  const int64_t r = rh / Hq;
+  const int64_t lse_stride = (int64_t)n_q * Hq, o_stride = lse_stride * 32;   // between ranges (float4 of O)
+  const float* pl = part_lse + (int64_t)h * n_q + r;
+  const float4* po = reinterpret_cast<const float4*>(part_o) + t;
+  float4* op = reinterpret_cast<float4*>(o) + ((r + row0) * Hq + h) * 32 + (t & 31);
+  float* lp = lse + (int64_t)h * lse_hs + r + row0;
+  const float la = accumulate ? *lp : -INFINITY;
+  float m = la;
+  for (int s = 0; s < nsplit; ++s) m = fmaxf(m, pl[s * lse_stride]);
+  const bool nothing = m == -INFINITY;
+  if (nothing && accumulate) return;                     // both empty: leave the running state
+  float tot = 0.f;
+  float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (accumulate) {
+    const float w = __expf(la - m);                      // exp(-inf) = 0
+    const float4 y = *op;
+    tot = w;
+    x.x = w * y.x; x.y = w * y.y; x.z = w * y.z; x.w = w * y.w;
+  }
+#pragma unroll 4
+  for (int s = 0; s < nsplit; ++s) {
+    const float w = nothing ? 1.f : __expf(pl[s * lse_stride] - m);   // nothing: the sum of zeros, or the NaN of a row of NaNs
+    const float4 y = po[s * o_stride];                   // an empty range has stored zeros
+    tot += w;
+    x.x += w * y.x; x.y += w * y.y; x.z += w * y.z; x.w += w * y.w;
+  }
+  const float inv = nothing ? 1.f : 1.f / tot;
+  x.x *= inv; x.y *= inv; x.z *= inv; x.w *= inv;
+  *op = x;
+  if ((t & 31) == 0) *lp = nothing ? -INFINITY : m + __logf(tot);
+}
+
+// dq[rows of the block] += sum of the partial results
+__global__ __launch_bounds__(256) void dq_combine_kernel(const float* __restrict__ part, int nsplit, int64_t n4, float* __restrict__ dq) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t >= n4) return;
+  const float4* p = reinterpret_cast<const float4*>(part) + t;
+  float4* out = reinterpret_cast<float4*>(dq) + t;
+  float4 x = *out;
+#pragma unroll 4
+  for (int s = 0; s < nsplit; ++s) {
+    const float4 y = p[s * n4];
+    x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
+  }
+  *out = x;
+}
+
+}  // namespace
+
+int cu_count() {
+  static int cu_of_device[64] = {};                     // 0 = not asked yet; the count never changes for a device
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) n = cu_of_device[dev];
+  if (n == 0) {
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+    if (dev >= 0 && dev < 64) cu_of_device[dev] = n;
+  }
+  return n;
+}
+
+// Only grids smaller than the chip are cut.  The count minimises an estimate in units of one workgroup's
+// time for a 64-key tile (2 us): rounds of workgroups x (tiles of a range + kStart to load Q and the first
+// tiles and to store the result) + the combining pass (a launch, and every partial result written and read
+// at about 4 TB/s = 8 MB per unit).  Documents shorten the ranges by an amount the host does not know;
+// half of the keys is assumed.
+// At most bwd_dkdv_partial_bytes() are used, so that a workspace larger than asked for changes no result.
+int pick_key_ranges(const StepArgs& a, int n_blocks, int64_t bytes_per_range, int64_t room) {
+  room = std::min(room, bwd_dkdv_partial_bytes());
+  constexpr double kStart = 2., kLaunch = 3., kBytesPerUnit = 8e6;
+  constexpr int kMaxRanges = 64;
+  const int n_cu = cu_count();
+  if (n_blocks >= n_cu || bytes_per_range <= 0) return 1;
+  int64_t keys = a.n_k;
+  if (a.mask == 1) keys = std::max<int64_t>(0, std::min<int64_t>(keys, (int64_t)a.q_pos0 + a.n_q - a.k_pos0));
+  if (a.cu != nullptr) keys /= 2;
+  const double tiles = (double)((keys + 63) / 64);
+  const int most = (int)std::min<int64_t>({kMaxRanges, room / bytes_per_range, (int64_t)(tiles / 4)});
+  int best = 1;
+  double best_cost = tiles + kStart;
+  for (int n = 2; n <= most; ++n) {
+    const int rounds = (n_blocks * n + n_cu - 1) / n_cu;
+    const double cost = rounds * (tiles / n + kStart) + kLaunch + 2. * n * (double)bytes_per_range / kBytesPerUnit;
+    if (cost < best_cost) { best = n; best_cost = cost; }
+  }
+  return best;
+}
+
+hipError_t launch_fwd_combine(const StepArgs& a, const float* part_o, const float* part_lse, int nsplit, hipStream_t stream) {
+  const int64_t n = (int64_t)a.n_q * a.Hq * 32;
+  fwd_combine_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(part_o, part_lse, nsplit, a.n_q, a.Hq, a.q_row0, a.o, a.lse,
+                                                                                 a.lse_hs, a.accumulate);
+  return hipGetLastError();
+}
+
+hipError_t launch_dq_combine(const StepArgs& a, const float* part, int nsplit, hipStream_t stream) {
+  const int64_t n4 = (int64_t)a.n_q * a.Hq * 32;
+  dq_combine_kernel<<<dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, stream>>>(part, nsplit, n4, a.dq + (int64_t)a.q_row0 * a.Hq * 128);
+  return hipGetLastError();
+}
+
+}  // namespace mmsp
