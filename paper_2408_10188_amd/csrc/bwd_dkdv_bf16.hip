@@ -96,29 +96,28 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
     kvh = blockIdx.x / (n_kt * nsplit);
     item = blockIdx.x % (n_kt * nsplit);
   }
-  const int kt = item / nsplit, split = item % nsplit;
+  int kt = item / nsplit;
+  const int split = item % nsplit;
+  const CuLocal cu = local_cu(a, reinterpret_cast<int32_t*>(lds + 8192), 64 * kWaves);
+  if (kMask && worth_ranking(a, cu, n_kt, a.k_pos0, a.k_pos0 + a.n_k - 1))
+    kt = heaviest_first(kt, n_kt, 64 * kWaves, reinterpret_cast<int*>(lds), [&](int i) { return query_tiles_of_keys(a, cu, i * kKeys, kKeys); });
   const int tile_key0 = kt * kKeys;
   const int key = tile_key0 + wave * 32 + col;           // block-relative key of this lane
   const bool live = key < a.n_k;
   const int keyc = min(key, a.n_k - 1);
 
   int rlo, rhi;                                          // query rows that see this lane's key
-  row_interval_of_key(a, keyc, rlo, rhi);
+  row_interval_of_key(a, cu, keyc, rlo, rhi);
+  const int w_hi_min = __builtin_amdgcn_readlane(rhi, 0);
   if (!live) { rlo = a.n_q; rhi = a.n_q - 1; }
+  const int w_lo_max = __builtin_amdgcn_readlane(rlo, 31);   // last key of the wavefront (n_q for a dead key: always mask)
   int t_lo, t_hi, dummy;
-  row_interval_of_key(a, tile_key0, t_lo, dummy);
-  row_interval_of_key(a, min(tile_key0 + kKeys, a.n_k) - 1, dummy, t_hi);
-  int w_lo_max, w_hi_min;
-  {
-    const int wk0 = min(tile_key0 + wave * 32, a.n_k - 1);
-    row_interval_of_key(a, wk0, dummy, w_hi_min);
-    w_lo_max = __shfl(rlo, 31);                          // last key of the wavefront (n_q for a dead key: always mask)
-  }
+  row_interval_of_key(a, cu, tile_key0, t_lo, dummy);
+  row_interval_of_key(a, cu, min(tile_key0 + kKeys, a.n_k) - 1, dummy, t_hi);
+  if (cu.copied) __syncthreads();                        // the tile copies may overwrite cu_seqlens
   // wavefront-uniform values, pinned to scalar registers so that the loop control is scalar too
   t_lo = __builtin_amdgcn_readfirstlane(t_lo);
   t_hi = __builtin_amdgcn_readfirstlane(t_hi);
-  w_lo_max = __builtin_amdgcn_readfirstlane(w_lo_max);
-  w_hi_min = __builtin_amdgcn_readfirstlane(w_hi_min);
   const int qt0 = t_lo / kBQ, qt1 = t_hi >= t_lo ? t_hi / kBQ : qt0 - 1;
   const int ntiles = qt1 - qt0 + 1;
   // this workgroup's share of the (query tile, head of the group) sequence: elements split,

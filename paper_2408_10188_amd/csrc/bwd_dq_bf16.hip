@@ -58,6 +58,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a,
     qt = n_items - 1 - blockIdx.x / a.Hq;
   }
   if (kPartial) { split = qt % nsplit; qt /= nsplit; }
+  const CuLocal cu = local_cu(a, reinterpret_cast<int32_t*>(lds + 8192), 64 * kWaves);
+  if (worth_ranking(a, cu, n_qt, a.q_pos0, a.q_pos0 + a.n_q - 1))
+    qt = heaviest_first(n_qt - 1 - qt, n_qt, 64 * kWaves, reinterpret_cast<int*>(lds), [&](int i) { return key_tiles_of_rows(a, cu, i * kBM, kBM); });
   const int kvh = h / a.group;
   const int tile_row0 = qt * kBM;
   const int row = tile_row0 + wave * 32 + col;          // block-relative query row of this lane
@@ -65,17 +68,14 @@ __global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a,
   const int rowc = min(row, a.n_q - 1);
 
   int lo, hi;
-  key_interval_of_row(a, rowc, lo, hi);
+  key_interval_of_row(a, cu, rowc, lo, hi);
   int t_lo, t_hi, dummy;
-  key_interval_of_row(a, tile_row0, t_lo, dummy);
-  key_interval_of_row(a, min(tile_row0 + kBM, a.n_q) - 1, dummy, t_hi);
-  int w_lo_max, w_hi_min;                               // wavefront: largest lo, smallest hi
-  int w_lo_min, w_hi_max;
-  {
-    const int wr0 = min(tile_row0 + wave * 32, a.n_q - 1), wr1 = min(tile_row0 + wave * 32 + 31, a.n_q - 1);
-    key_interval_of_row(a, wr0, w_lo_min, w_hi_min);
-    key_interval_of_row(a, wr1, w_lo_max, w_hi_max);
-  }
+  key_interval_of_row(a, cu, tile_row0, t_lo, dummy);
+  key_interval_of_row(a, cu, min(tile_row0 + kBM, a.n_q) - 1, dummy, t_hi);
+  // wavefront: smallest and largest lo and hi, those of its first and last row
+  const int w_lo_min = __builtin_amdgcn_readlane(lo, 0), w_hi_min = __builtin_amdgcn_readlane(hi, 0);
+  const int w_lo_max = __builtin_amdgcn_readlane(lo, 31), w_hi_max = __builtin_amdgcn_readlane(hi, 31);
+  if (cu.copied) __syncthreads();                        // the tile copies may overwrite cu_seqlens
   int kt0 = t_lo / kBN, kt1 = t_hi >= t_lo ? t_hi / kBN : kt0 - 1;   // inclusive tile range
   kt0 = __builtin_amdgcn_readfirstlane(kt0);
   kt1 = __builtin_amdgcn_readfirstlane(kt1);
@@ -84,10 +84,6 @@ __global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a,
     kt0 = first + (int)((int64_t)total * split / nsplit);
     kt1 = first + (int)((int64_t)total * (split + 1) / nsplit) - 1;
   }
-  w_lo_max = __builtin_amdgcn_readfirstlane(w_lo_max);
-  w_hi_min = __builtin_amdgcn_readfirstlane(w_hi_min);
-  w_lo_min = __builtin_amdgcn_readfirstlane(w_lo_min);
-  w_hi_max = __builtin_amdgcn_readfirstlane(w_hi_max);
 
   // ---- asynchronous tile fetch ----
   const int64_t kv_off = ((int64_t)a.k_row0 * a.kv_ts + (int64_t)kvh * a.kv_hs) * 2;

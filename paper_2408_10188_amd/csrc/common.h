@@ -42,11 +42,36 @@ struct BwdWorkspace {
 
 __host__ __device__ inline int64_t tiles_of(int64_t rows) { return (rows + 63) / 64; }
 
+// Where a kernel reads cu_seqlens from: memory, or LDS that its workgroup has copied it to.  The searches below
+// are chains of dependent reads, about 0.4 us each from memory and a tenth of that from LDS; a
+// workgroup makes three of them before its first copy is issued, and one per tile that it ranks.
+struct CuGlobal {
+  const int32_t* p;
+  __device__ __forceinline__ int operator[](int i) const { return p[i]; }
+};
+struct CuLocal {
+  const int32_t* p;
+  const int32_t* in_lds;
+  bool copied;
+  __device__ __forceinline__ int operator[](int i) const { return copied ? in_lds[i] : p[i]; }
+};
+constexpr int kMaxLocalDocs = 1023;                     // 4 KiB of LDS
+// Copies cu_seqlens to `lds` (kMaxLocalDocs + 1 ints) if it fits; every thread of the workgroup calls it.
+__device__ __forceinline__ CuLocal local_cu(const StepArgs& a, int32_t* lds, int n_threads) {
+  const bool copied = a.cu != nullptr && a.n_docs <= kMaxLocalDocs;
+  if (copied) {
+    for (int i = threadIdx.x; i <= a.n_docs; i += n_threads) lds[i] = a.cu[i];
+    __syncthreads();
+  }
+  return CuLocal{a.cu, lds, copied};
+}
+
 // Visible key interval [lo, hi] (indices inside the block's key range, already clipped to
 // [0, n_k-1]) of the query row with block-relative index i.  Empty when lo > hi.
 // A pair is visible iff the key position is <= the query position (causal-diag only) and
 // both positions lie in the same cu_seqlens document (when given).
-__device__ __forceinline__ void key_interval_of_row(const StepArgs& a, int i, int& lo, int& hi) {
+template <class Cu>
+__device__ __forceinline__ void key_interval_of_row(const StepArgs& a, const Cu& cu, int i, int& lo, int& hi) {
   const int p = a.q_pos0 + i;
   int lo_pos = INT32_MIN / 2, hi_pos = INT32_MAX / 2;
   if (a.mask == 1) hi_pos = p;
@@ -55,11 +80,11 @@ __device__ __forceinline__ void key_interval_of_row(const StepArgs& a, int i, in
     int L = 0, R = a.n_docs;          // invariant: cu[L] <= p (if p >= 0) < cu[R] (if inside)
     // positions outside every document see nothing; the empty intervals are chosen so that
     // lo and hi stay non-decreasing in the row index
-    if (p < a.cu[0]) { lo = 0; hi = -1; return; }
-    if (p >= a.cu[a.n_docs]) { lo = a.n_k; hi = a.n_k - 1; return; }
-    while (R - L > 1) { int m = (L + R) >> 1; if (a.cu[m] <= p) L = m; else R = m; }
-    lo_pos = max(lo_pos, a.cu[L]);
-    hi_pos = min(hi_pos, a.cu[L + 1] - 1);
+    if (p < cu[0]) { lo = 0; hi = -1; return; }
+    if (p >= cu[a.n_docs]) { lo = a.n_k; hi = a.n_k - 1; return; }
+    while (R - L > 1) { int m = (L + R) >> 1; if (cu[m] <= p) L = m; else R = m; }
+    lo_pos = max(lo_pos, cu[L]);
+    hi_pos = min(hi_pos, cu[L + 1] - 1);
   }
   lo = max(0, lo_pos - a.k_pos0);
   hi = min(a.n_k - 1, hi_pos - a.k_pos0);
@@ -67,20 +92,74 @@ __device__ __forceinline__ void key_interval_of_row(const StepArgs& a, int i, in
 
 // Mirror image: interval [lo, hi] of block-relative query rows that see the key with
 // block-relative index j (clipped to [0, n_q-1]).
-__device__ __forceinline__ void row_interval_of_key(const StepArgs& a, int j, int& lo, int& hi) {
+template <class Cu>
+__device__ __forceinline__ void row_interval_of_key(const StepArgs& a, const Cu& cu, int j, int& lo, int& hi) {
   const int p = a.k_pos0 + j;
   int lo_pos = INT32_MIN / 2, hi_pos = INT32_MAX / 2;
   if (a.mask == 1) lo_pos = p;
   if (a.cu != nullptr) {
     int L = 0, R = a.n_docs;
-    if (p < a.cu[0]) { lo = 0; hi = -1; return; }
-    if (p >= a.cu[a.n_docs]) { lo = a.n_q; hi = a.n_q - 1; return; }
-    while (R - L > 1) { int m = (L + R) >> 1; if (a.cu[m] <= p) L = m; else R = m; }
-    lo_pos = max(lo_pos, a.cu[L]);
-    hi_pos = min(hi_pos, a.cu[L + 1] - 1);
+    if (p < cu[0]) { lo = 0; hi = -1; return; }
+    if (p >= cu[a.n_docs]) { lo = a.n_q; hi = a.n_q - 1; return; }
+    while (R - L > 1) { int m = (L + R) >> 1; if (cu[m] <= p) L = m; else R = m; }
+    lo_pos = max(lo_pos, cu[L]);
+    hi_pos = min(hi_pos, cu[L + 1] - 1);
   }
   lo = max(0, lo_pos - a.q_pos0);
   hi = min(a.n_q - 1, hi_pos - a.q_pos0);
+}
+
+// Workgroups are dispatched in index order as CUs come free, so the heaviest should come first.  Without
+// documents the index order does that by itself (work falls or rises steadily under a causal mask); documents
+// shorter than the block restart the triangle at every boundary, and heavy tiles that start last leave most CUs
+// waiting for them.  The host does not know the documents, so every workgroup ranks the n tiles by itself:
+// the index of the tile with the want-th most work (work(i) < 2^20; earlier tiles first among equals).  Costs
+// about 2 us for 160 tiles; above kMaxRanked there are many rounds of workgroups, whose ends average
+// out, and neighbours in the sequence should stay neighbours in time for the sake of L2.
+// 20011 tokens packed from clips of up to 4700, 7/1 heads: dK/dV 509 -> 487 us, forward 224 -> 216, dQ 284 -> 277
+// (with cu_seqlens read from LDS); what is left there is the longest document against the mean.
+// scratch: LDS of at least kMaxRanked + 1 ints, free to be overwritten when the function returns.
+constexpr int kMaxRanked = 512;
+template <class Work>
+__device__ __forceinline__ int heaviest_first(int want, int n, int n_threads, int* scratch, Work work) {
+  for (int i = threadIdx.x; i < n; i += n_threads) scratch[i] = work(i) * kMaxRanked + (kMaxRanked - 1 - i);
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += n_threads) {
+    const int mine = scratch[i];
+    int rank = 0;
+    for (int j = 0; j < n; ++j) rank += scratch[j] > mine;
+    if (rank == want) scratch[kMaxRanked] = i;
+  }
+  __syncthreads();
+  const int found = __builtin_amdgcn_readfirstlane(scratch[kMaxRanked]);
+  __syncthreads();
+  return found;
+}
+
+// Whether ranking n tiles over the positions [first, last] can change their order.
+template <class Cu>
+__device__ __forceinline__ bool worth_ranking(const StepArgs& a, const Cu& cu, int n, int first, int last) {
+  if (a.cu == nullptr || n > kMaxRanked || n < 3) return false;
+  if (first < cu[0] || last >= cu[a.n_docs]) return true;
+  int L = 0, R = a.n_docs;
+  while (R - L > 1) { int m = (L + R) >> 1; if (cu[m] <= first) L = m; else R = m; }
+  return last >= cu[L + 1];                             // positions of one document: sorted already
+}
+
+// Key tiles of 64 that a query tile of n rows visits / query tiles of 64 that a key tile visits.
+template <class Cu>
+__device__ __forceinline__ int key_tiles_of_rows(const StepArgs& a, const Cu& cu, int row0, int n) {
+  int lo, hi, dummy;
+  key_interval_of_row(a, cu, row0, lo, dummy);
+  key_interval_of_row(a, cu, min(row0 + n, a.n_q) - 1, dummy, hi);
+  return hi >= lo ? min(hi / 64 - lo / 64 + 1, (1 << 20) - 1) : 0;
+}
+template <class Cu>
+__device__ __forceinline__ int query_tiles_of_keys(const StepArgs& a, const Cu& cu, int key0, int n) {
+  int lo, hi, dummy;
+  row_interval_of_key(a, cu, key0, lo, dummy);
+  row_interval_of_key(a, cu, min(key0 + n, a.n_k) - 1, dummy, hi);
+  return hi >= lo ? min(hi / 64 - lo / 64 + 1, (1 << 20) - 1) : 0;
 }
 
 // ---- launchers (each enqueues on `stream` and returns hipGetLastError()) ----

@@ -121,7 +121,7 @@ __global__ __launch_bounds__(64 * kWaves) void fwd_f32_kernel(StepArgs a) {
   const int row0 = blockIdx.x * kRows, h = blockIdx.y, kvh = h / a.group;
   const int rowc = min(row0 + col, a.n_q - 1);
   int lo, hi;
-  key_interval_of_row(a, rowc, lo, hi);
+  key_interval_of_row(a, CuGlobal{a.cu}, rowc, lo, hi);
   const int lo_first = __builtin_amdgcn_readlane(lo, 0), hi_first = __builtin_amdgcn_readlane(hi, 0);
   const int lo_last = __builtin_amdgcn_readlane(lo, 15), hi_last = __builtin_amdgcn_readlane(hi, 15);
   const int kb0 = lo_first / kRows, kb1 = hi_last >= lo_first ? hi_last / kRows : kb0 - 1;
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(64 * kWaves) void bwd_dq_f32_kernel(StepArgs a) {
   const int row0 = blockIdx.x * kRows, h = blockIdx.y, kvh = h / a.group;
   const int rowc = min(row0 + col, a.n_q - 1);
   int lo, hi;
-  key_interval_of_row(a, rowc, lo, hi);
+  key_interval_of_row(a, CuGlobal{a.cu}, rowc, lo, hi);
   const int lo_first = __builtin_amdgcn_readlane(lo, 0), hi_first = __builtin_amdgcn_readlane(hi, 0);
   const int lo_last = __builtin_amdgcn_readlane(lo, 15), hi_last = __builtin_amdgcn_readlane(hi, 15);
   const int kb0 = lo_first / kRows, kb1 = hi_last >= lo_first ? hi_last / kRows : kb0 - 1;
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(64 * kWaves) void bwd_dkdv_f32_kernel(StepArgs a) {
   const int key0 = blockIdx.x * kRows, kvh = blockIdx.y;
   const int keyc = min(key0 + col, a.n_k - 1);
   int lo, hi;
-  row_interval_of_key(a, keyc, lo, hi);
+  row_interval_of_key(a, CuGlobal{a.cu}, keyc, lo, hi);
   const int lo_first = __builtin_amdgcn_readlane(lo, 0), hi_first = __builtin_amdgcn_readlane(hi, 0);
   const int lo_last = __builtin_amdgcn_readlane(lo, 15), hi_last = __builtin_amdgcn_readlane(hi, 15);
   const int qb0 = lo_first / kRows, n_qb = hi_last >= lo_first ? hi_last / kRows - qb0 + 1 : 0;

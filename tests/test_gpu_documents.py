@@ -1,0 +1,21 @@
+"""Blocks of many documents: tiles ranked by their work, cu_seqlens searched in LDS (up to 1023 documents) and in
+memory (more), against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch  # noqa: F401  (before the library: both must share torch's HIP runtime)
+
+from paper_2408_10188_amd import binding as B
+from tests.test_gpu_parity import _run_step
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_docs", [3, 40, 1023, 1024, 1200])
+@pytest.mark.parametrize("mask", [B.MMSP_MASK_CAUSAL_DIAG, B.MMSP_MASK_FULL])
+def test_many_documents(n_docs, mask):
+    T = 1500
+    cuts = np.sort(np.random.default_rng(n_docs).choice(np.arange(1, T), n_docs - 1, replace=False))
+    cu = [0, *cuts.tolist(), T]
+    _run_step(True, 4, 2, 128, T, T, dict(q_row0=0, n_q=T, k_row0=0, n_k=T, mask=mask), cu=cu, seed=n_docs)
+    # a block of rows from the middle, on keys that begin and end elsewhere, with positions outside every document at either end
+    _run_step(True, 3, 3, 128, 900, 1300, dict(q_row0=10, n_q=870, k_row0=5, n_k=1290, mask=mask, q_pos0=700, k_pos0=-20), cu=cu, seed=n_docs)
