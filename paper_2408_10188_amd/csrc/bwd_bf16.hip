@@ -49,30 +49,23 @@ int64_t bwd_bf16_workspace_bytes(int Hq, int64_t n_q) {
   return 2 * Hq * tiles_of(n_q) * 64 * (int64_t)sizeof(float) + bwd_dkdv_partial_bytes();
 }
 
-// Lays out the workspace of one backward call and fills the padded row statistics; the
-// partial-sum area follows them.
-hipError_t bwd_bf16_prepare(const StepArgs& a, BwdWorkspace& w, hipStream_t stream) {
-  const int64_t t = tiles_of(a.n_q);
-  char* p = a.ws;
-  float* nl2 = reinterpret_cast<float*>(p);  p += a.Hq * t * 64 * sizeof(float);
-  float* ndl = reinterpret_cast<float*>(p);   p += a.Hq * t * 64 * sizeof(float);
-  w.nl2 = nl2; w.ndl = ndl; w.partial = reinterpret_cast<float*>(p); w.n_qtiles = (int32_t)t;
-  return launch_bwd_stats(a.lse_final, a.delta, a.lse_hs, a.Hq, a.q_row0, a.n_q, nl2, ndl, stream);
-}
-
+// A call that wants all three gradients has the dQ kernel write the row statistics, which its
+// workgroups hold anyway: a launch less (4 to 5 us a step; 320 rows x 4 heads, two steps forward and
+// backward: 120 -> 117 us).
 hipError_t launch_bwd_bf16(const StepArgs& a, hipStream_t stream) {
+  BwdWorkspace w;                                        // statistics, then the partial-sum area
+  w.n_qtiles = (int32_t)tiles_of(a.n_q);
+  w.nl2 = reinterpret_cast<float*>(a.ws);
+  w.ndl = w.nl2 + (int64_t)a.Hq * w.n_qtiles * 64;
+  w.partial = w.ndl + (int64_t)a.Hq * w.n_qtiles * 64;
   if (a.dq != nullptr) {
-    hipError_t e = launch_bwd_dq_bf16(a, stream);
+    const hipError_t e = launch_bwd_dq_bf16(a, a.dk != nullptr ? &w : nullptr, stream);
+    if (e != hipSuccess || a.dk == nullptr) return e;
+  } else {
+    const hipError_t e = launch_bwd_stats(a.lse_final, a.delta, a.lse_hs, a.Hq, a.q_row0, a.n_q, w.nl2, w.ndl, stream);
     if (e != hipSuccess) return e;
   }
-  if (a.dk != nullptr) {
-    BwdWorkspace w;
-    hipError_t e = bwd_bf16_prepare(a, w, stream);
-    if (e != hipSuccess) return e;
-    e = launch_bwd_dkdv_bf16(a, w, stream);
-    if (e != hipSuccess) return e;
-  }
-  return hipGetLastError();
+  return launch_bwd_dkdv_bf16(a, w, stream);
 }
 
 }  // namespace mmsp

@@ -24,7 +24,8 @@ constexpr int kCopies = 16 / kWaves;
 // kPartial: nsplit workgroups share the key tiles of every query tile, each stores its share of dQ in
 // part [nsplit][n_q][Hq][128] for launch_dq_combine.
 template <bool kPartial>
-__global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_qt, int xcd_per_kv, int nsplit, float* part) {
+__global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_qt, int xcd_per_kv, int nsplit, float* part,
+                                                                     BwdWorkspace stats) {
   // LDS map: the three K slots in [0, 48 KiB), the three V slots in [48 KiB, 96 KiB); slots are
   // selected at compile time (the loop is unrolled three tiles deep).  An LDS instruction's
   // immediate offset reaches 64 KiB, so the V reads go through per-lane base registers that
@@ -131,6 +132,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a,
   const float Dl = a.delta[(int64_t)h * a.lse_hs + r];
   const float neg_l2 = L == -INFINITY ? -INFINITY : -L * kLog2e;   // a row that saw nothing: P = 0
   const float c = a.scale * kLog2e;
+  // Row statistics for the dK/dV kernel that follows; rows up to the next whole 64 count as rows that saw nothing.
+  if (stats.nl2 != nullptr && split == 0 && half == 0 && row < stats.n_qtiles * 64) {
+    const int64_t at = (int64_t)h * stats.n_qtiles * 64 + row;
+    stats.nl2[at] = live ? neg_l2 : -INFINITY;
+    stats.ndl[at] = live ? -Dl : 0.f;
+  }
 
   // dP's accumulator starts from -delta (one value per lane: a lane holds one query), so dP - delta
   // needs no subtraction: 32 of a tile's 150 vector instructions.
@@ -251,7 +258,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a,
 
 }  // namespace
 
-hipError_t launch_bwd_dq_bf16(const StepArgs& a, hipStream_t stream) {
+hipError_t launch_bwd_dq_bf16(const StepArgs& a, const BwdWorkspace* stats_out, hipStream_t stream) {
+  const BwdWorkspace no_stats = {nullptr, nullptr, nullptr, 0}, st = stats_out != nullptr ? *stats_out : no_stats;
   const int n_qt = (a.n_q + kBM - 1) / kBM;
   // the partial results lie where the dK/dV kernel, later on the same stream, keeps its own
   const int64_t stats = bwd_bf16_workspace_bytes(a.Hq, a.n_q) - bwd_dkdv_partial_bytes();
@@ -263,11 +271,11 @@ hipError_t launch_bwd_dq_bf16(const StepArgs& a, hipStream_t stream) {
   }
   if (nsplit > 1) {
     float* part = reinterpret_cast<float*>(a.ws + stats);
-    bwd_dq_bf16_kernel<true><<<dim3(n_blocks), dim3(64 * kWaves), 0, stream>>>(a, n_qt, xcd_per_kv, nsplit, part);
+    bwd_dq_bf16_kernel<true><<<dim3(n_blocks), dim3(64 * kWaves), 0, stream>>>(a, n_qt, xcd_per_kv, nsplit, part, st);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : launch_dq_combine(a, part, nsplit, stream);
   }
-  bwd_dq_bf16_kernel<false><<<dim3(n_blocks), dim3(64 * kWaves), 0, stream>>>(a, n_qt, xcd_per_kv, 1, nullptr);
+  bwd_dq_bf16_kernel<false><<<dim3(n_blocks), dim3(64 * kWaves), 0, stream>>>(a, n_qt, xcd_per_kv, 1, nullptr, st);
   return hipGetLastError();
 }
 

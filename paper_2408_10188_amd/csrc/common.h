@@ -34,8 +34,8 @@ struct StepArgs {
 
 // Workspace views of one backward call (all inside the caller's workspace).
 struct BwdWorkspace {
-  const float* nl2;    // -LSE*log2e, [Hq][n_qtiles*64], -inf where LSE = -inf and in the padding
-  const float* ndl;    // -delta,     [Hq][n_qtiles*64], 0 in the padding
+  float* nl2;          // -LSE*log2e, [Hq][n_qtiles*64], -inf where LSE = -inf and in the padding
+  float* ndl;          // -delta,     [Hq][n_qtiles*64], 0 in the padding
   float* partial;      // partial dK then dV of split key tiles, bwd_dkdv_partial_bytes() in all
   int32_t n_qtiles;
 };
@@ -185,8 +185,8 @@ hipError_t launch_dq_combine(const StepArgs& a, const float* part, int nsplit, h
 hipError_t launch_bwd_dkdv_bf16(const StepArgs& a, const BwdWorkspace& w, hipStream_t stream);
 int64_t bwd_bf16_workspace_bytes(int Hq, int64_t n_q);
 int64_t bwd_dkdv_partial_bytes();
-hipError_t launch_bwd_dq_bf16(const StepArgs& a, hipStream_t stream);
-hipError_t bwd_bf16_prepare(const StepArgs& a, BwdWorkspace& w, hipStream_t stream);
+// stats: where to write the padded row statistics on the way, or nullptr
+hipError_t launch_bwd_dq_bf16(const StepArgs& a, const BwdWorkspace* stats, hipStream_t stream);
 
 hipError_t launch_zigzag_gather(const void* seq, void* shards, int64_t T, int N, int64_t row_bytes, hipStream_t stream);
 hipError_t launch_zigzag_scatter(const void* shards, void* seq, int64_t T, int N, int64_t row_bytes, hipStream_t stream);
