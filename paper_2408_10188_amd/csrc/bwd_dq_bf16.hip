@@ -141,7 +141,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a,
 
   // dP's accumulator starts from -delta (one value per lane: a lane holds one query), so dP - delta
   // needs no subtraction: 32 of a tile's 150 vector instructions (8 x 8192 rows, 28/4 heads, forward and
-  // backward: 3% of the pass).
+  // backward: 15.63 -> 15.19 ms).
   f32x16 ndl;
 #pragma unroll
   for (int i = 0; i < 16; ++i) ndl[i] = -Dl;
