@@ -34,15 +34,12 @@ __global__ __launch_bounds__(256) void merge_kernel(float* __restrict__ o_acc, f
   const int h = (int)(rh % Hq);
   const int64_t r = rh / Hq + row0;
   const int64_t off = (r * Hq + h) * (int64_t)d + c * 4;
-  float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (!kMerge) o = *reinterpret_cast<const float4*>(o_acc + off);
+  // Also read where the running LSE is -inf: a row whose scores held a NaN has LSE = -inf and O = NaN, which 0 * O keeps.
+  float4 o = *reinterpret_cast<const float4*>(o_acc + off);
   if (kMerge) {
     const int64_t li = h * lse_hs + r;
-    const float4 p = *reinterpret_cast<const float4*>(o_part + off);
     const float la = lse_acc[li], lp = lse_part[li];
-    // Rows without a running result yet (all of them at the first merge) need not read one: a third of the
-    // bytes.  8192 rows x 28 heads: 60 -> 42 us; with one, waiting for its LSE first changes nothing (68 us).
-    if (la != -INFINITY) o = *reinterpret_cast<const float4*>(o_acc + off);
+    const float4 p = *reinterpret_cast<const float4*>(o_part + off);
     const float m = fmaxf(la, lp);
     float wa, wb, ln;
     if (m == -INFINITY) { wa = 0.f; wb = 0.f; ln = -INFINITY; }
