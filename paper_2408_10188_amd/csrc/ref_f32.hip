@@ -196,7 +196,7 @@ __global__ __launch_bounds__(64 * kWaves) void fwd_f32_kernel(StepArgs a) {
       const float f = ms[w][r] == -INFINITY ? (ls[w][r] == 0.f ? 0.f : 1.f) : expf(ms[w][r] - mt);
       const float4 y = *reinterpret_cast<const float4*>(p + w * kPartFloats<D>);
       lt = fmaf(f, ls[w][r], lt);
-      if (f != 0.f) { o.x = fmaf(f, y.x, o.x); o.y = fmaf(f, y.y, o.y); o.z = fmaf(f, y.z, o.z); o.w = fmaf(f, y.w, o.w); }
+      o.x = fmaf(f, y.x, o.x); o.y = fmaf(f, y.y, o.y); o.z = fmaf(f, y.z, o.z); o.w = fmaf(f, y.w, o.w);   // 0 * NaN stays NaN
     }
     const float inv = lt > 0.f ? 1.f / lt : 0.f;
     const float lse_part = lt > 0.f ? mt + logf(lt) : -INFINITY;

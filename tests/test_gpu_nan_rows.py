@@ -31,3 +31,16 @@ def test_ring_keeps_nan_rows(dtype, d, lanes, fused, rank, where):
     for o in (out["o_acc"], out["o_final"]):
         assert torch.equal(torch.isnan(o).any(2), want)
         assert torch.equal(torch.isnan(o).all(2), want)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_f32_wavefront_without_weight_keeps_its_nan(d):
+    """Keys 0 to 15, one wavefront's share, lie 200 below all others, so that its weight in the merge is exp(-200) = 0."""
+    n_q, n_k, key = 20, 128, 3
+    q, k, v = (torch.zeros(n, 1, d, device=DEV) for n in (n_q, n_k, n_k))
+    q[:, 0, 0], k[:16, 0, 0], v[:] = math.sqrt(d), -200.0, 1.0
+    k[key, 0, 1] = math.nan
+    shape = ring.shape_for(q, k, B.MMSP_F32, n_q)
+    o, lse = torch.zeros(n_q, 1, d, device=DEV), torch.zeros(1, n_q, device=DEV)
+    B.mmsp_attn_step_fwd(shape, B.make_block(0, n_q, 0, n_k, B.MMSP_MASK_FULL), q, k, v, o, lse, False)
+    assert bool(torch.isnan(o).all()) and bool((lse == -math.inf).all())
