@@ -371,7 +371,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
   l += __shfl_xor(l, 32);
   const bool empty = !(l > 0.f);
   const float inv = empty ? 0.f : 1.f / l;
-  const float lse_part = empty ? -INFINITY : (m * c + __builtin_amdgcn_logf(l)) * kLn2;   // v_log_f32 is log2
+  // A row of NaNs reports LSE = -inf, a range's share of one NaN: the combining pass has to tell it from an empty range.
+  const float lse_part = (kResult == kPartial ? l == 0.f : empty) ? -INFINITY : (m * c + __builtin_amdgcn_logf(l)) * kLn2;   // v_log_f32 is log2
   if (!live) return;
   const int64_t r = a.q_row0 + row;
   float* op = (kResult == kPartial ? part_o + ((int64_t)split * a.n_q + row) * a.Hq * 128 : a.o + r * a.Hq * 128) + h * 128 + half * 4;

@@ -30,7 +30,18 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(const float* __restric
   float* lp = lse + (int64_t)h * lse_hs + r + row0;
   const float la = accumulate ? *lp : -INFINITY;
   float m = la;
-  for (int s = 0; s < nsplit; ++s) m = fmaxf(m, pl[s * lse_stride]);
+  bool nan = false;
+  for (int s = 0; s < nsplit; ++s) {
+    const float L = pl[s * lse_stride];
+    m = fmaxf(m, L);
+    nan |= L != L;
+  }
+  if (nan) {                                             // as a workgroup that has all keys leaves such a row
+    if (accumulate && la == -INFINITY) return;
+    *op = make_float4(NAN, NAN, NAN, NAN);
+    if ((t & 31) == 0 && !accumulate) *lp = -INFINITY;
+    return;
+  }
   const bool nothing = m == -INFINITY;
   if (nothing && accumulate) return;                     // both empty: leave the running state
   float tot = 0.f;
@@ -43,7 +54,7 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(const float* __restric
   }
 #pragma unroll 4
   for (int s = 0; s < nsplit; ++s) {
-    const float w = nothing ? 1.f : __expf(pl[s * lse_stride] - m);   // nothing: the sum of zeros, or the NaN of a row of NaNs
+    const float w = nothing ? 1.f : __expf(pl[s * lse_stride] - m);   // nothing: the sum of zeros, or the NaN of 0 * inf in V
     const float4 y = po[s * o_stride];                   // an empty range has stored zeros
     tot += w;
     x.x += w * y.x; x.y += w * y.y; x.z += w * y.z; x.w += w * y.w;

@@ -44,3 +44,30 @@ def test_f32_wavefront_without_weight_keeps_its_nan(d):
     o, lse = torch.zeros(n_q, 1, d, device=DEV), torch.zeros(1, n_q, device=DEV)
     B.mmsp_attn_step_fwd(shape, B.make_block(0, n_q, 0, n_k, B.MMSP_MASK_FULL), q, k, v, o, lse, False)
     assert bool(torch.isnan(o).all()) and bool((lse == -math.inf).all())
+
+
+@pytest.mark.parametrize("running", [None, -math.inf, 1.0])       # overwrite / merge into an empty and into a full running result
+@pytest.mark.parametrize("where", ["query", "key"])
+def test_key_ranges_report_nan_rows_as_one_workgroup_does(running, where):
+    hq, n_q, n_k = 2, 40, 3000
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    q, k, v = (torch.randn(s, device=DEV, generator=gen).bfloat16() for s in ((n_q, hq, 128), (n_k, 1, 128), (n_k, 1, 128)))
+    if where == "query":
+        q[7, 1] = math.nan
+    else:
+        k[n_k - 20, 0, 3] = math.nan                              # the rows from the 20th on see it
+    shape = ring.shape_for(q, k, B.MMSP_BF16, n_q)
+    block = B.make_block(0, n_q, 0, n_k, B.MMSP_MASK_CAUSAL_DIAG, n_k - n_q, 0)
+    got = []
+    for room in (0, 64 << 20):                                    # one workgroup for all keys, then several
+        ws = torch.zeros(room + 16, dtype=torch.uint8, device=DEV)
+        o, lse = torch.full((n_q, hq, 128), 0.25, device=DEV), torch.full((hq, n_q), 0.0 if running is None else running, device=DEV)
+        B.mmsp_attn_step_fwd(shape, block, q, k, v, o, lse, running is not None, ws, room)
+        assert (room > 0) == bool(ws.any())                       # the partial results were kept there
+        got.append((o, lse))
+    (o1, lse1), (o2, lse2) = got
+    assert torch.equal(torch.isnan(o1), torch.isnan(o2)) and (bool(torch.isnan(o1).any()) or running == -math.inf)
+    assert torch.equal(torch.isfinite(lse1), torch.isfinite(lse2))
+    # two bf16 roundings of P against different references: 2^-8 of a mean of unit values, over many keys
+    torch.testing.assert_close(o1.nan_to_num(), o2.nan_to_num(), atol=2e-2, rtol=0)
+    torch.testing.assert_close(lse1, lse2, atol=1e-3, rtol=0)
