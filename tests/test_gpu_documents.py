@@ -19,3 +19,10 @@ def test_many_documents(n_docs, mask):
     _run_step(True, 4, 2, 128, T, T, dict(q_row0=0, n_q=T, k_row0=0, n_k=T, mask=mask), cu=cu, seed=n_docs)
     # a block of rows from the middle, on keys that begin and end elsewhere, with positions outside every document at either end
     _run_step(True, 3, 3, 128, 900, 1300, dict(q_row0=10, n_q=870, k_row0=5, n_k=1290, mask=mask, q_pos0=700, k_pos0=-20), cu=cu, seed=n_docs)
+
+
+@pytest.mark.parametrize("cu", [[0, 63, 64, 65, 200], [0, 30, 129, 190, 200], [64, 128, 150]])
+@pytest.mark.parametrize("k_pos0", [0, 10, -70])
+def test_rows_that_begin_in_other_tiles_than_their_workgroup(cu, k_pos0):
+    """Of 200 rows in one workgroup some see its first key tile, whose maximum is their reference, some only later ones, some none."""
+    _run_step(True, 2, 1, 128, 200, 210, dict(q_row0=0, n_q=200, k_row0=0, n_k=210, mask=B.MMSP_MASK_CAUSAL_DIAG, q_pos0=0, k_pos0=k_pos0), cu=cu)
