@@ -99,7 +99,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
   int kt = item / nsplit;
   const int split = item % nsplit;
   const CuLocal cu = local_cu(a, reinterpret_cast<int32_t*>(lds + 8192), 64 * kWaves);
-  if (kMask && worth_ranking(a, cu, n_kt, a.k_pos0, a.k_pos0 + a.n_k - 1))
+  if (kMask && worth_ranking(a, cu, a.k_pos0, a.k_pos0 + a.n_k - 1))
     kt = heaviest_first(kt, n_kt, 64 * kWaves, reinterpret_cast<int*>(lds), [&](int i) { return query_tiles_of_keys(a, cu, i * kKeys, kKeys); });
   const int tile_key0 = kt * kKeys;
   const int key = tile_key0 + wave * 32 + col;           // block-relative key of this lane
@@ -499,7 +499,8 @@ constexpr int kSplitMaxRanges = 8;
 
 int64_t bwd_dkdv_partial_bytes() { return 2LL * kSplitMaxBlocks * kKeys * 128 * (int64_t)sizeof(float); }
 
-hipError_t launch_bwd_dkdv_bf16(const StepArgs& a, const BwdWorkspace& w, hipStream_t stream) {
+hipError_t launch_bwd_dkdv_bf16(const StepArgs& args, const BwdWorkspace& w, hipStream_t stream) {
+  StepArgs a = args;
   const int n_kt = (a.n_k + kKeys - 1) / kKeys;
   // One workgroup per (key tile, KV head) fills the chip only if there are about as many as
   // CUs; with fewer, cut every key tile's query sequence into ranges.
@@ -513,6 +514,7 @@ hipError_t launch_bwd_dkdv_bf16(const StepArgs& a, const BwdWorkspace& w, hipStr
   int nsplit = min(target / base_blocks, kSplitMaxRanges);
   if (nsplit < 2) nsplit = 1;
   const int n_items = n_kt * nsplit;
+  a.rank = may_rank(a, n_kt, n_items * a.Hkv, a.group, 7);
   int xcd_per_kv = 0, n_blocks = n_items * a.Hkv;
   if (8 % a.Hkv == 0) {
     xcd_per_kv = 8 / a.Hkv;

@@ -60,7 +60,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a,
   }
   if (kPartial) { split = qt % nsplit; qt /= nsplit; }
   const CuLocal cu = local_cu(a, reinterpret_cast<int32_t*>(lds + 8192), 64 * kWaves);
-  if (worth_ranking(a, cu, n_qt, a.q_pos0, a.q_pos0 + a.n_q - 1))
+  if (worth_ranking(a, cu, a.q_pos0, a.q_pos0 + a.n_q - 1))
     qt = heaviest_first(n_qt - 1 - qt, n_qt, 64 * kWaves, reinterpret_cast<int*>(lds), [&](int i) { return key_tiles_of_rows(a, cu, i * kBM, kBM); });
   const int kvh = h / a.group;
   const int tile_row0 = qt * kBM;
@@ -259,13 +259,15 @@ __global__ __launch_bounds__(64 * kWaves, 2) void bwd_dq_bf16_kernel(StepArgs a,
 
 }  // namespace
 
-hipError_t launch_bwd_dq_bf16(const StepArgs& a, const BwdWorkspace* stats_out, hipStream_t stream) {
+hipError_t launch_bwd_dq_bf16(const StepArgs& args, const BwdWorkspace* stats_out, hipStream_t stream) {
+  StepArgs a = args;
   const BwdWorkspace no_stats = {nullptr, nullptr, nullptr, 0}, st = stats_out != nullptr ? *stats_out : no_stats;
   const int n_qt = (a.n_q + kBM - 1) / kBM;
   // the partial results lie where the dK/dV kernel, later on the same stream, keeps its own
   const int64_t stats = bwd_bf16_workspace_bytes(a.Hq, a.n_q) - bwd_dkdv_partial_bytes();
   const int nsplit = pick_key_ranges(a, n_qt * a.Hq, (int64_t)a.n_q * a.Hq * 128 * sizeof(float), a.ws_bytes - stats);
   int xcd_per_kv = 0, n_blocks = n_qt * nsplit * a.Hq;
+  a.rank = may_rank(a, n_qt, n_blocks, 1, 5);
   if (8 % a.Hkv == 0) {
     xcd_per_kv = 8 / a.Hkv;
     n_blocks = 8 * ((a.group * n_qt * nsplit + xcd_per_kv - 1) / xcd_per_kv);

@@ -30,6 +30,7 @@ struct StepArgs {
   int32_t accumulate;           // fwd: merge into running state; bwd: add to dk/dv
   char* ws;                     // caller's workspace (bf16; nullptr or too small for a cut: no cut)
   int64_t ws_bytes;
+  int32_t rank;                 // bf16 kernels: whether workgroups may rank their tiles (may_rank)
 };
 
 // Workspace views of one backward call (all inside the caller's workspace).
@@ -113,11 +114,8 @@ __device__ __forceinline__ void row_interval_of_key(const StepArgs& a, const Cu&
 // documents the index order does that by itself (work falls or rises steadily under a causal mask); documents
 // shorter than the block restart the triangle at every boundary, and heavy tiles that start last leave most CUs
 // waiting for them.  The host does not know the documents, so every workgroup ranks the n tiles by itself:
-// the index of the tile with the want-th most work (work(i) < 2^20; earlier tiles first among equals).  Costs
-// about 2 us for 160 tiles; above kMaxRanked there are many rounds of workgroups, whose ends average
-// out, and neighbours in the sequence should stay neighbours in time for the sake of L2.
-// 20011 tokens packed from clips of up to 4700, 7/1 heads: dK/dV 509 -> 487 us, forward 224 -> 216, dQ 284 -> 277
-// (with cu_seqlens read from LDS); what is left there is the longest document against the mean.
+// the index of the tile with the want-th most work (work(i) < 2^20; earlier tiles first among equals).
+// That costs every workgroup some us, the more the more tiles there are; when it pays: may_rank.
 // scratch: LDS of at least kMaxRanked + 1 ints, free to be overwritten when the function returns.
 constexpr int kMaxRanked = 512;
 template <class Work>
@@ -136,10 +134,10 @@ __device__ __forceinline__ int heaviest_first(int want, int n, int n_threads, in
   return found;
 }
 
-// Whether ranking n tiles over the positions [first, last] can change their order.
+// Whether ranking tiles over the positions [first, last] can change their order.
 template <class Cu>
-__device__ __forceinline__ bool worth_ranking(const StepArgs& a, const Cu& cu, int n, int first, int last) {
-  if (a.cu == nullptr || n > kMaxRanked || n < 3) return false;
+__device__ __forceinline__ bool worth_ranking(const StepArgs& a, const Cu& cu, int first, int last) {
+  if (!a.rank) return false;
   if (first < cu[0] || last >= cu[a.n_docs]) return true;
   int L = 0, R = a.n_docs;
   while (R - L > 1) { int m = (L + R) >> 1; if (cu[m] <= first) L = m; else R = m; }
@@ -178,6 +176,7 @@ hipError_t launch_bwd_stats(const float* lse, const float* delta, int64_t lse_hs
 
 // Query tiles whose key range is cut into several workgroups (forward, dQ), see split.hip.
 int cu_count();
+int32_t may_rank(const StepArgs& a, int n_tiles, int n_blocks, int heads_per_tile, int max_rounds);
 int pick_key_ranges(const StepArgs& a, int n_blocks, int64_t bytes_per_range, int64_t room);
 hipError_t launch_fwd_combine(const StepArgs& a, const float* part_o, const float* part_lse, int nsplit, hipStream_t stream);
 hipError_t launch_dq_combine(const StepArgs& a, const float* part, int nsplit, hipStream_t stream);

@@ -73,7 +73,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
   }
   if (kResult == kPartial) { split = qt % nsplit; qt /= nsplit; }
   const CuLocal cu = local_cu(a, reinterpret_cast<int32_t*>(lds + 8192), 64 * kWaves);
-  if (worth_ranking(a, cu, n_qt, a.q_pos0, a.q_pos0 + a.n_q - 1))
+  if (worth_ranking(a, cu, a.q_pos0, a.q_pos0 + a.n_q - 1))
     qt = heaviest_first(n_qt - 1 - qt, n_qt, 64 * kWaves, reinterpret_cast<int*>(lds), [&](int i) { return key_tiles_of_rows(a, cu, i * kBM, kBM); });
   const int kvh = h / a.group;
   const int tile_row0 = qt * kBM;
@@ -419,10 +419,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
 
 }  // namespace
 
-hipError_t launch_fwd_bf16(const StepArgs& a, hipStream_t stream) {
+hipError_t launch_fwd_bf16(const StepArgs& args, hipStream_t stream) {
+  StepArgs a = args;
   const int n_qt = (a.n_q + kBM - 1) / kBM;
   const int nsplit = pick_key_ranges(a, n_qt * a.Hq, (int64_t)a.n_q * a.Hq * 129 * sizeof(float), a.ws_bytes);
   int xcd_per_kv = 0, n_blocks = n_qt * nsplit * a.Hq;
+  a.rank = may_rank(a, n_qt, n_blocks, 1, 5);
   if (8 % a.Hkv == 0) {
     xcd_per_kv = 8 / a.Hkv;
     n_blocks = 8 * ((a.group * n_qt * nsplit + xcd_per_kv - 1) / xcd_per_kv);

@@ -26,3 +26,10 @@ def test_many_documents(n_docs, mask):
 def test_rows_that_begin_in_other_tiles_than_their_workgroup(cu, k_pos0):
     """Of 200 rows in one workgroup some see its first key tile, whose maximum is their reference, some only later ones, some none."""
     _run_step(True, 2, 1, 128, 200, 210, dict(q_row0=0, n_q=200, k_row0=0, n_k=210, mask=B.MMSP_MASK_CAUSAL_DIAG, q_pos0=0, k_pos0=k_pos0), cu=cu)
+
+
+@pytest.mark.parametrize("hq,hkv", [(80, 40), (28, 14)])     # enough workgroups that tiles are ranked, by the second for dK/dV in cut ranges
+@pytest.mark.parametrize("cu,q_pos0", [([0, 300, 900], 0), ([0, 620], 0), ([130, 131, 700, 1000], 90)])
+@pytest.mark.parametrize("mask", [B.MMSP_MASK_CAUSAL_DIAG, B.MMSP_MASK_FULL])
+def test_ranked_tiles(hq, hkv, cu, q_pos0, mask):
+    _run_step(True, hq, hkv, 128, 900, 900, dict(q_row0=0, n_q=900, k_row0=0, n_k=900, mask=mask, q_pos0=q_pos0, k_pos0=q_pos0), cu=cu)
