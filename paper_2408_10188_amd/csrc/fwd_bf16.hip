@@ -422,7 +422,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void fwd_bf16_kernel(StepArgs a, in
 hipError_t launch_fwd_bf16(const StepArgs& args, hipStream_t stream) {
   StepArgs a = args;
   const int n_qt = (a.n_q + kBM - 1) / kBM;
-  const int nsplit = pick_key_ranges(a, n_qt * a.Hq, (int64_t)a.n_q * a.Hq * 129 * sizeof(float), a.ws_bytes);
+  // The slowest query tile counts: one tile lies anywhere in a document, of eight one lies late in a long one.
+  const double mean_documents = 1. + (n_qt < 8 ? n_qt - 1 : 7) / 7.;
+  const int nsplit = pick_key_ranges(a, n_qt * a.Hq, (int64_t)a.n_q * a.Hq * 129 * sizeof(float), a.ws_bytes, mean_documents);
   int xcd_per_kv = 0, n_blocks = n_qt * nsplit * a.Hq;
   a.rank = may_rank(a, n_qt, n_blocks, 1, 5);
   if (8 % a.Hkv == 0) {

@@ -93,11 +93,16 @@ int cu_count() {
   return n;
 }
 
+// Mean length of the documents up to the block's last position: exact for a whole sequence, too short for its earlier
+// parts (n_docs counts the later documents too).
+static double mean_document(const StepArgs& a) {
+  return (double)std::max(0, std::max(a.q_pos0 + a.n_q, a.k_pos0 + a.n_k)) / a.n_docs;
+}
+
 // Whether workgroups may rank their tiles (heaviest_first).  Every workgroup pays for it, the more the more tiles there
 // are, and what it saves at the end of a launch is about one tile's work, so it is done
 //  * from 1.2 rounds of workgroups (within one all start together) to max_rounds (the ends of many average out);
-//  * where the rows of an average document, times the heads that a tile takes, outweigh rounds x tiles.  The documents'
-//    mean length is taken as the block's last position / n_docs: exact for a whole sequence, shorter otherwise.
+//  * where the rows of an average document, times the heads that a tile takes, outweigh rounds x tiles.
 // Packs of clips of 200..4700 / 300..2500 / 100..1200 / 60..300 tokens, time without ranking over time with it:
 //   forward, 7/1   79 tiles (2.2 rounds)  1.19 1.12 1.11 0.95   200 tiles (5.5)  1.04 0.97 0.92 0.83
 //   forward, 28/4  16 tiles (1.75)        0.97 1.17 1.06 0.93   80 tiles (8.8)   0.97 0.95 0.92 0.89
@@ -107,18 +112,19 @@ int32_t may_rank(const StepArgs& a, int n_tiles, int n_blocks, int heads_per_til
   if (a.cu == nullptr || a.n_docs < 2 || a.n_docs > kMaxLocalDocs || n_tiles < 3 || n_tiles > kMaxRanked) return 0;
   const double rounds = (double)n_blocks / cu_count();
   if (rounds < 1.2 || rounds > max_rounds) return 0;
-  const int last = std::max(a.q_pos0 + a.n_q, a.k_pos0 + a.n_k);
-  const double rows = (double)last / a.n_docs;
-  return heads_per_tile * rows >= (heads_per_tile > 1 ? 200. : 400.) + rounds * n_tiles;
+  return heads_per_tile * mean_document(a) >= (heads_per_tile > 1 ? 200. : 400.) + rounds * n_tiles;
 }
 
 // Only grids smaller than the chip are cut.  The count minimises an estimate in units of one workgroup's
 // time for a 64-key tile (2 us): rounds of workgroups x (tiles of a range + kStart to load Q and the first
 // tiles and to store the result) + the combining pass (a launch, and every partial result written and read
-// at about 4 TB/s = 8 MB per unit).  Documents shorten the ranges by an amount the host does not know;
-// half of the keys is assumed.
+// at about 4 TB/s = 8 MB per unit).
+// Documents shorten the visible keys by an amount the host does not know; taken are `mean_documents` documents
+// of the mean length (the block's last position / n_docs), see the callers.  A cut that the documents leave with empty ranges
+// costs 5 to 10 us; half of all keys, whatever n_docs, was such a cut for every block of short documents (100 rows on
+// 8192 keys, 28/4 heads, documents of 60..300: forward 16 us uncut, 25 us cut, 14.6 us by this rule, which does not cut).
 // At most bwd_dkdv_partial_bytes() are used, so that a workspace larger than asked for changes no result.
-int pick_key_ranges(const StepArgs& a, int n_blocks, int64_t bytes_per_range, int64_t room) {
+int pick_key_ranges(const StepArgs& a, int n_blocks, int64_t bytes_per_range, int64_t room, double mean_documents) {
   room = std::min(room, bwd_dkdv_partial_bytes());
   constexpr double kStart = 2., kLaunch = 3., kBytesPerUnit = 8e6;
   constexpr int kMaxRanges = 64;
@@ -126,7 +132,7 @@ int pick_key_ranges(const StepArgs& a, int n_blocks, int64_t bytes_per_range, in
   if (n_blocks >= n_cu || bytes_per_range <= 0) return 1;
   int64_t keys = a.n_k;
   if (a.mask == 1) keys = std::max<int64_t>(0, std::min<int64_t>(keys, (int64_t)a.q_pos0 + a.n_q - a.k_pos0));
-  if (a.cu != nullptr) keys /= 2;
+  if (a.cu != nullptr) keys = std::min(keys, (int64_t)(mean_documents * mean_document(a)));
   const double tiles = (double)((keys + 63) / 64);
   const int most = (int)std::min<int64_t>({kMaxRanges, room / bytes_per_range, (int64_t)(tiles / 4)});
   int best = 1;

@@ -64,3 +64,17 @@ def test_a_row_of_nans_stays_one():
     B.mmsp_attn_step_fwd(shape, B.make_block(0, n_q, 0, n_k, B.MMSP_MASK_FULL), q, k, v, o, lse, False, ws, ws.numel())
     nan = torch.isnan(o).all(2)
     assert bool(nan[7, 1]) and int(torch.isnan(o).any(2).sum()) == 1
+
+
+@pytest.mark.parametrize("docs,cut", [(1, True), (4, True), (150, False)])
+def test_short_documents_are_not_cut(docs, cut):
+    """The host knows the documents' number only; with many of them a row sees few keys and ranges would be empty."""
+    hq, n_q, n_k = 8, 100, 6000
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    q, k, v = (torch.randn(s, device=DEV, generator=gen).bfloat16() for s in ((n_q, hq, 128), (n_k, 1, 128), (n_k, 1, 128)))
+    cu = torch.linspace(0, n_k, docs + 1, device=DEV).to(torch.int32)
+    shape = ring.shape_for(q, k, B.MMSP_BF16, n_q)
+    ws = torch.zeros(64 << 20, dtype=torch.uint8, device=DEV)
+    o, lse = torch.zeros(n_q, hq, 128, device=DEV), torch.zeros(hq, n_q, device=DEV)
+    B.mmsp_attn_step_fwd(shape, B.make_block(0, n_q, 0, n_k, B.MMSP_MASK_CAUSAL_DIAG, n_k - n_q, 0, cu, docs), q, k, v, o, lse, False, ws, ws.numel())
+    assert bool(ws.any()) == cut
