@@ -41,8 +41,9 @@ constexpr int kDepth = 4;                        // LDS operand reads in flight 
 // back one v_accvgpr_read each.  Of the 518 instructions of a tile those copies and the 32
 // subtractions of delta (now the accumulator's start value) were 96.  The compiler does not know
 // that these are matrix instructions, so the waits it would insert are the caller's:
-//  * A comes straight from an LDS read and B (AGPRs) never changes: no vector instruction writes
-//    an operand shortly before;
+//  * no vector instruction may write an operand in the two wait states before.  A comes straight from
+//    an LDS read, B (AGPRs) never changes, and the accumulator input of dP, read from LDS too, is pinned before
+//    the S product that precedes its first use, so that copies the compiler may need come before that product;
 //  * a result may be read by a vector instruction only behind four more matrix instructions
 //    (each holds the issue of the next for its eight passes; nineteen wait states are required), or behind
 //    MMSP_RESULT_WAIT: MMSP_PIN of the result at that place keeps earlier readers out.
@@ -298,6 +299,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
     lds_barrier();
     {
       load_ndl(dp_nx, st0, 0);
+      MMSP_PIN(dp_nx);
 #pragma unroll
       for (int ks = 0; ks < 8; ++ks) {
         const u32x4 oq_ = *reinterpret_cast<const u32x4*>(qs0 + na[ks]), oo_ = *reinterpret_cast<const u32x4*>(os0 + na[ks]);
@@ -355,6 +357,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
             const int n = ph * 16 + i, ks = i >> 1;
             u32x4 op = oq[n & (kDepth - 1)];
             MMSP_PIN(op);
+            if (i == 0) MMSP_PIN(dp_nx);
             if (i == 0) mfma32_v_first(s_nx, op, kreg[0]);
             else if ((i & 1) == 0) mfma32_v(s_nx, op, kreg[ks]);
             else mfma32_v(dp_nx, op, vreg[ks]);
