@@ -6,6 +6,7 @@
 // workgroups on 256 CUs, 720 us for 32768 keys.  With the keys cut in nine ranges, each storing
 // its partial result in the caller's workspace, the same step takes 126 us.
 #include <algorithm>
+#include <atomic>
 
 #include "common.h"
 
@@ -83,12 +84,12 @@ __global__ __launch_bounds__(256) void dq_combine_kernel(const float* __restrict
 }  // namespace
 
 int cu_count() {
-  static int cu_of_device[64] = {};                     // 0 = not asked yet; the count never changes for a device
+  static std::atomic<int> cu_of_device[64] = {};        // 0 = not asked yet; the count never changes for a device
   int dev = 0, n = 0;
-  if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) n = cu_of_device[dev];
+  if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) n = cu_of_device[dev].load(std::memory_order_relaxed);
   if (n == 0) {
     if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-    if (dev >= 0 && dev < 64) cu_of_device[dev] = n;
+    if (dev >= 0 && dev < 64) cu_of_device[dev].store(n, std::memory_order_relaxed);
   }
   return n;
 }
