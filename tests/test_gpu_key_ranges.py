@@ -49,8 +49,37 @@ def test_workspace_of_any_size(ranges, accumulate):
     assert max_abs(to_host64(o), o_ref) <= NORTH_STAR_TOL["bf16"]["o"]
     assert max_abs(to_host64(lse), l_ref + (math.log(2.0) if accumulate else 0.0)) <= NORTH_STAR_TOL["bf16"]["lse"]
     assert bool((ws[given:] == 77).all())
-    if ranges < 2:
-        assert bool((ws == 77).all())
+    assert bool((ws == 77).all()) == (ranges < 2)         # with room for two ranges the keys are cut
+
+
+@pytest.mark.parametrize("gradients", ["dq", "all"])
+@pytest.mark.parametrize("n_q,n_k", [(77, 2000), (300, 1984)])
+def test_dq_ranges_stay_in_the_workspace(gradients, n_q, n_k):
+    hq, hkv, d, scale = 4, 2, 128, 1 / math.sqrt(128)
+    rng = np.random.default_rng(6)
+    q, k, v = (synth.bf16_round(rng.standard_normal(s, dtype=np.float32) * 0.5) for s in ((n_q, hq, d), (n_k, hkv, d), (n_k, hkv, d)))
+    do = synth.bf16_round(rng.standard_normal((n_q, hq, d), dtype=np.float32))
+    blk = dict(q_row0=0, n_q=n_q, k_row0=0, n_k=n_k, q_pos0=n_k - n_q, k_pos0=0, mask=B.MMSP_MASK_CAUSAL_DIAG)
+    q64, k64, v64, do64 = (x.astype(np.float64) for x in (q, k, v, do))
+    o_ref, l_ref = orc.step_fwd(q64, k64, v64, blk, scale, None)
+    delta = orc.delta(do64, o_ref)
+    ref = orc.step_bwd(q64, k64, v64, do64, l_ref, delta, blk, scale, None)
+    qd, kd, vd, dod = (to_dev(x, True) for x in (q, k, v, do))
+    lse, dl = (to_dev(x.astype(np.float32), False) for x in (l_ref, delta))
+    shape = ring.shape_for(qd, kd, B.MMSP_BF16, n_q, scale)
+    given = B.mmsp_workspace_bytes(shape, n_q, n_k, True)
+    ws = torch.full((given + 4096,), 77, dtype=torch.uint8, device=DEV)
+    dq = torch.zeros(n_q, hq, d, device=DEV)
+    dk, dv = (torch.full((n_k, hkv, d), math.nan, device=DEV) for _ in range(2))
+    both = gradients == "all"
+    B.mmsp_attn_step_bwd(shape, B.make_block(0, n_q, 0, n_k, blk["mask"], blk["q_pos0"], 0), qd, kd, vd, None, dod, lse, dl, False, dq,
+                         dk if both else None, dv if both else None, False, ws, given)
+    for got, want in zip((dq, dk, dv) if both else (dq,), ref):
+        assert max_abs(to_host64(got), want) <= NORTH_STAR_TOL["bf16"]["g"]
+    assert bool((ws[given:] == 77).all())
+    stats = 2 * hq * 4 * ((n_q + 63) // 64 * 64)          # row statistics, written for dK/dV only; the partial results lie behind them
+    assert bool((ws[:stats] == 77).all()) != both
+    assert bool((ws[stats:stats + 2 * n_q * hq * d * 4] != 77).any())
 
 
 def test_a_row_of_nans_stays_one():
