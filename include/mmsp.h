@@ -195,9 +195,13 @@ size_t mmsp_workspace_bytes(const mmsp_shape* shape, int64_t n_q_max, int64_t n_
  *   partial is applied in the kernel's epilogue (same arithmetic as mmsp_attn_merge).
  * Rows outside [q_row0, q_row0+n_q) are not touched.  A row that sees nothing gets
  * O_part = 0, LSE_part = -inf (and leaves a running result unchanged).
- * workspace: at least mmsp_workspace_bytes(shape, n_q, n_k, 0) bytes (may be NULL when 0).  Given
- *   more (the backward's size is plenty), a bf16 block with too few query rows to fill the GPU has its
- *   keys shared out to several workgroups, whose partial results use up to 64 MiB of it. */
+ * workspace: at least mmsp_workspace_bytes(shape, n_q, n_k, 0) bytes, which is 0 (may be NULL).  Given a
+ *   16-byte-aligned one all the same, a bf16 block with too few query rows to fill the GPU (fewer than
+ *   256 tiles of 256 rows and head) and many keys has its keys shared out to several workgroups: 203 rows x 28 heads on 32768
+ *   keys take 122 us instead of 783.  Each workgroup's share uses n_q x n_q_heads x 516 bytes, all together at most 64 MiB;
+ *   what lies beyond 64 MiB is not used, so the size that the backward asks for serves any block.  The number of
+ *   shares depends on the bytes given (below 64 MiB), and with it the rounding of O and LSE: calls that must
+ *   agree bit for bit need workspaces of the same size, or none. */
 mmsp_status mmsp_attn_step_fwd(const mmsp_shape* shape, const mmsp_block* blk,
                                const void* q, const void* k, const void* v,
                                float* o, float* lse, int accumulate,

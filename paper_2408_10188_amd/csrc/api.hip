@@ -92,8 +92,8 @@ mmsp_status device_result(hipError_t e, const char* what) {
   return fail(MMSP_ERR_DEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 
-// Only the bf16 backward needs scratch: padded row statistics and the partial dK / dV sums of
-// split key tiles (dK/dV kernel).
+// Only the bf16 backward needs scratch: padded row statistics and partial dQ, dK and dV of work that was
+// cut into several workgroups.  The forward can use some for partial results (key ranges) but needs none.
 size_t needed_workspace(const mmsp_shape* s, int64_t n_q, int64_t n_k, bool backward) {
   (void)n_k;
   if (backward) return (size_t)mmsp::bwd_bf16_workspace_bytes(s->n_q_heads, n_q);

@@ -13,8 +13,9 @@
 // Each recomputes S and dP (7 tile products in total instead of 5) in exchange for
 // exclusive ownership of its outputs.
 //
-// Workspace of a backward call (dK/dV kernel only): [-LSE*log2e | -delta] padded to whole
-// 64-row tiles, then the area for partial dK / dV sums of split key tiles.
+// Workspace of a backward call: [-LSE*log2e | -delta] padded to whole 64-row tiles (read by the dK/dV
+// kernel, written by the dQ kernel or, without one, by bwd_stats_kernel), then the area for the partial dQ of cut
+// query tiles and, later on the same stream, the partial dK / dV sums of split key tiles.
 #include "common.h"
 
 namespace mmsp {

@@ -37,7 +37,7 @@ struct StepArgs {
 struct BwdWorkspace {
   float* nl2;          // -LSE*log2e, [Hq][n_qtiles*64], -inf where LSE = -inf and in the padding
   float* ndl;          // -delta,     [Hq][n_qtiles*64], 0 in the padding
-  float* partial;      // partial dK then dV of split key tiles, bwd_dkdv_partial_bytes() in all
+  float* partial;      // bwd_dkdv_partial_bytes(): partial dQ of cut query tiles, then dK and dV of split key tiles
   int32_t n_qtiles;
 };
 

@@ -8,7 +8,8 @@
 // with partial results of its own that meet in LDS at the end, so the loop has no barrier; the
 // products run on v_mfma_f32_16x16x4_f32 (fp32 operands and accumulation) with operands loaded
 // straight from memory: a block's rows are used once per wavefront, so LDS tiles would buy nothing.
-// The same pass now takes 72 us, most of it the nine launches, and is closer to 64 bits (3.3e-7, was 5.6e-7).
+// The same pass now takes 72 us (nine launches, the larger ones 9 to 19 us each for chains of two to four blocks per
+// wavefront) and is closer to 64 bits (3.2e-7, was 5.8e-7).
 //
 // v_mfma_f32_16x16x4_f32, C[16x16] += A[16x4] B[4x16], lane L: A row L % 16, k = L / 16; B column L % 16,
 // k = L / 16; C column L % 16, rows (L / 16) * 4 + i, i = 0..3.  Which k a slot stands for is free as long

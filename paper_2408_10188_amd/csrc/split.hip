@@ -3,8 +3,8 @@
 //
 // A workgroup owns 256 query rows of one head and fills a CU by itself, so a block of few rows leaves
 // most of the chip idle for as long as one workgroup needs for all keys: 203 rows x 28 heads are 28
-// workgroups on 256 CUs, 720 us for 32768 keys.  With the keys cut in nine ranges, each storing
-// its partial result in the caller's workspace, the same step takes 126 us.
+// workgroups on 256 CUs, 783 us for 32768 keys with the final cast.  With the keys cut in nine ranges, each
+// storing its partial result in the caller's workspace, the same two calls take 122 us.
 #include <algorithm>
 #include <atomic>
 
