@@ -78,7 +78,8 @@ mmsp_status check_block(const mmsp_shape* s, const mmsp_block* b) {
 mmsp::StepArgs make_args(const mmsp_shape* s, const mmsp_block* b) {
   mmsp::StepArgs a;
   memset(&a, 0, sizeof(a));
-  a.Hq = s->n_q_heads; a.Hkv = s->n_kv_heads; a.group = s->n_q_heads / s->n_kv_heads; a.d = s->head_dim;
+  a.Hq = s->n_q_heads; a.Hkv = s->n_kv_heads; a.d = s->head_dim;
+  mmsp::set_group(a, s->n_q_heads / s->n_kv_heads);
   a.q_ts = s->q_tok_stride; a.q_hs = s->q_head_stride; a.kv_ts = s->kv_tok_stride; a.kv_hs = s->kv_head_stride;
   a.lse_hs = s->lse_head_stride; a.scale = s->softmax_scale;
   a.q_row0 = (int32_t)b->q_row0; a.n_q = (int32_t)b->n_q; a.k_row0 = (int32_t)b->k_row0; a.n_k = (int32_t)b->n_k;

@@ -267,7 +267,7 @@ hipError_t launch_bwd_dq_bf16(const StepArgs& args, const BwdWorkspace* stats_ou
   // the partial results lie where the dK/dV kernel, later on the same stream, keeps its own
   const int64_t stats = bwd_bf16_workspace_bytes(a.Hq, a.n_q) - bwd_dkdv_partial_bytes();
   // Two documents' keys for any number of query tiles (the forward: one to two): a tile costs more here, so a cut pays sooner.
-  const int nsplit = pick_key_ranges(a, n_qt * a.Hq, (int64_t)a.n_q * a.Hq * 128 * sizeof(float), a.ws_bytes - stats, 2.);
+  const int nsplit = pick_key_ranges(a, (int64_t)a.n_q * a.Hq * 128 * sizeof(float), a.ws_bytes - stats, 2.).count;
   int xcd_per_kv = 0, n_blocks = n_qt * nsplit * a.Hq;
   a.rank = may_rank(a, n_qt, n_blocks, 1, 5);
   if (8 % a.Hkv == 0) {

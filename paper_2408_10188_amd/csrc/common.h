@@ -21,6 +21,7 @@ struct StepArgs {
   const int32_t* cu;            // cu_seqlens or nullptr
   // shape
   int32_t Hq, Hkv, group, d;
+  uint32_t group_magic;         // set_group()
   int64_t q_ts, q_hs, kv_ts, kv_hs, lse_hs;
   float scale;
   // block
@@ -32,6 +33,20 @@ struct StepArgs {
   int64_t ws_bytes;
   int32_t rank;                 // bf16 kernels: whether workgroups may rank their tiles (may_rank)
 };
+
+// Heads per KV head, and what row_of_pair() needs to divide by it: floor(2^32 / group) + 1, 0 for a group of one.
+inline void set_group(StepArgs& a, int group) {
+  a.group = group;
+  a.group_magic = group > 1 ? (uint32_t)((1ull << 32) / (uint32_t)group) + 1 : 0;
+}
+// i / group for 0 <= i < 2^31.  The rounded-up reciprocal exceeds 1 / group by at most 2^-32, so the product's upper half
+// is the quotient or, at most, one more.  (A division of two runtime integers is some 35 dependent instructions, and a workgroup
+// needs several before its first copy.)
+__device__ __forceinline__ int row_of_pair(const StepArgs& a, int i) {
+  if (a.group_magic == 0) return i;
+  const uint32_t q = __umulhi((uint32_t)i, a.group_magic);
+  return (int)(q - (q * (uint32_t)a.group > (uint32_t)i ? 1u : 0u));
+}
 
 // Workspace views of one backward call (all inside the caller's workspace).
 struct BwdWorkspace {
@@ -177,7 +192,8 @@ hipError_t launch_bwd_stats(const float* lse, const float* delta, int64_t lse_hs
 // Query tiles whose key range is cut into several workgroups (forward, dQ), see split.hip.
 int cu_count();
 int32_t may_rank(const StepArgs& a, int n_tiles, int n_blocks, int heads_per_tile, int max_rounds);
-int pick_key_ranges(const StepArgs& a, int n_blocks, int64_t bytes_per_range, int64_t room, double mean_documents);
+struct KeyRanges { int waves, count; };                 // wavefronts of a workgroup, workgroups that share a tile's keys
+KeyRanges pick_key_ranges(const StepArgs& a, int64_t bytes_per_range, int64_t room, double mean_documents);
 hipError_t launch_fwd_combine(const StepArgs& a, const float* part_o, const float* part_lse, int nsplit, hipStream_t stream);
 hipError_t launch_dq_combine(const StepArgs& a, const float* part, int nsplit, hipStream_t stream);
 

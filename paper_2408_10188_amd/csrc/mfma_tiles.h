@@ -154,4 +154,68 @@ __device__ __forceinline__ DmaOffs<kCopies> dma_s_offsets(int64_t row_stride_ele
   return t;
 }
 
+// ---------------------------------------------------------------------------------------
+// TileG: the same [64 rows][128 cols] tile for kernels that are short of registers.  Four rows (the 1 KiB of one
+// copy) form a group of 1040 bytes: chunk c of row r lies at position c ^ (4 (r & 3)) of its row, and the 16 bytes of padding shift
+// consecutive groups by one chunk.  Both read patterns of TileS stay free of bank conflicts (rows 4 g + m of a phase
+// differ in m, which moves them by 64 bytes, or in g, which moves them by 16), but only the upper two bits of
+// a chunk index are mixed with the row, so half of the addresses are another's plus a constant that
+// an instruction's offset field holds: four address registers per read pattern instead of eight.
+// ---------------------------------------------------------------------------------------
+constexpr int kGroupPitch = 1024 + 16;
+constexpr int kTileGBytes = 16 * kGroupPitch;
+constexpr int kTileGRows32 = 8 * kGroupPitch;          // 32 rows further
+constexpr int kTileGRows16 = 4 * kGroupPitch;          // 16 rows further
+constexpr int kTileGRows8 = 2 * kGroupPitch;           // 8 rows further: second transposing read of an operand
+
+__device__ __forceinline__ int tile_g_offset(int row, int chunk /*0..15*/) {
+  return (row >> 2) * kGroupPitch + (row & 3) * 256 + ((chunk ^ ((row & 3) << 2)) << 4);
+}
+// k index along d: operand of k-step ks is 16 bytes at tile_g_nat(lane, ks / 2) + (ks & 1) * 32
+__device__ __forceinline__ int tile_g_nat(int lane, int ks_pair) { return tile_g_offset(lane & 31, ks_pair * 4 + (lane >> 5)); }
+// k index along the tokens: two transposing reads, at tile_g_tr(lane, db) + 16 rows per token group, and kTileGRows8 further
+__device__ __forceinline__ int tile_g_tr(int lane, int db) {
+  const int grp = lane >> 4, a = lane & 3, m = (lane >> 2) & 3;
+  return tile_g_offset((grp >> 1) * 4 + m, db * 4 + (grp & 1) * 2 + (a >> 1)) + (a & 1) * 8;
+}
+
+// Copies of a tensor's tiles into TileG slots, one wavefront-copy (4 rows) at a time.  A tile's address is
+// wavefront-uniform; the lane's part of the address is the same for every whole tile, and in one that is not
+// whole it stops at the last row (`limit`), so that rows past the end repeat it.  A copy costs four instructions of which
+// one is a vector instruction: with the address of every copy computed from its tile's index in 64 bits a wavefront spent
+// more issue slots on scalar arithmetic than on matrix instructions.
+template <int kCopies>
+struct TileCopier {
+  static constexpr int W = 16 / kCopies;               // wavefronts that share a tile
+  uint32_t tile_bytes;
+  int last, ragged;                                    // last tile to fetch, the one that is not whole (or -1)
+  int lds_wave;                                        // start of the wavefront's first copy inside a slot
+  uint32_t off[kCopies], ragged_limit;
+  __device__ __forceinline__ void init(int64_t row_stride_elems, int rows, int last_tile, int wave, int lane) {
+    const uint32_t row_bytes = (uint32_t)row_stride_elems * 2, chunk = ((lane & 15) ^ ((lane >> 4) << 2)) << 4;
+    tile_bytes = 64 * row_bytes;
+    last = last_tile;
+    ragged = rows % 64 != 0 ? rows / 64 : -1;
+    lds_wave = __builtin_amdgcn_readfirstlane(wave) * kGroupPitch;
+    ragged_limit = (ragged >= 0 ? rows % 64 - 1 : 63) * row_bytes + chunk;
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) off[i] = (4 * (wave + i * W) + (lane >> 4)) * row_bytes + chunk;
+  }
+  struct Tile { const char* base; uint32_t limit; };
+  // tile t of the tensor whose tile 0 starts at `first`; past the last tile that one again
+  __device__ __forceinline__ Tile tile(const char* first, int t) const {
+    t = min(t, last);
+    return {first + (uint64_t)(uint32_t)t * tile_bytes, t == ragged ? ragged_limit : 0xffffffffu};
+  }
+  // the wavefront's copy i of a tile into the slot at byte kSlot of the kernel's LDS array (which starts at LDS address 0)
+  __device__ __forceinline__ void copy(const Tile& x, int i, int slot_offset) const {
+    const uint32_t o = min(off[i], x.limit);
+    asm volatile("s_add_i32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_wave), "v"(o), "s"(x.base), "i"(slot_offset + i * W * kGroupPitch) : "memory", "scc");
+  }
+  __device__ __forceinline__ void copy_to(const Tile& x, int i, int slot_offset) const {   // the same, slot known at run time only
+    const uint32_t o = min(off[i], x.limit);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_wave + slot_offset + i * W * kGroupPitch), "v"(o), "s"(x.base) : "memory");
+  }
+};
+
 }  // namespace mmsp

@@ -2,9 +2,9 @@
 // and the kernels that combine the partial results.
 //
 // A workgroup owns 256 query rows of one head and fills a CU by itself, so a block of few rows leaves
-// most of the chip idle for as long as one workgroup needs for all keys: 203 rows x 28 heads are 28
-// workgroups on 256 CUs, 783 us for 32768 keys with the final cast.  With the keys cut in nine ranges, each
-// storing its partial result in the caller's workspace, the same two calls take 122 us.
+// most of the chip idle for as long as one workgroup needs for all keys: 203 rows x 28 heads are 24
+// workgroups on 256 CUs, 783 us for 32768 keys with the final cast.  With the keys cut in ranges, each
+// storing its partial result in the caller's workspace, the same two calls take 107 us.
 #include <algorithm>
 #include <atomic>
 
@@ -13,57 +13,83 @@
 namespace mmsp {
 namespace {
 
-// (O, LSE) of a row = log-sum-exp merge of its partial results, and with the running one when accumulate.  One
-// thread per 4 elements of d; the 32 threads of a (row, head) lie in one wavefront, whose lanes have
-// all read the running LSE before lane 0 of the 32 replaces it.
+// (O, LSE) of a row = log-sum-exp merge of its partial results, and with the running one when accumulate.  32 threads
+// take 4 elements of d each; kGroups of them share out the ranges of a (row, head), so that a chain of dependent loads and sums is
+// nsplit / kGroups long, and meet in LDS.
+template <int kGroups>
 __global__ __launch_bounds__(256) void fwd_combine_kernel(const float* __restrict__ part_o, const float* __restrict__ part_lse, int nsplit,
                                                           int n_q, int Hq, int row0, float* __restrict__ o, float* __restrict__ lse,
                                                           int64_t lse_hs, bool accumulate) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t rh = t >> 5;
-  if (rh >= (int64_t)n_q * Hq) return;
+  constexpr int kRows = 8 / kGroups;                    // (row, head)s of a workgroup
+  __shared__ float4 xs[8][32];
+  __shared__ float ms[8], ts[8];
+  const int c = threadIdx.x & 31, team = threadIdx.x >> 5, g = team % kGroups;
+  const int64_t n = (int64_t)n_q * Hq, rh = (int64_t)blockIdx.x * kRows + team / kGroups;
+  const bool live = rh < n;
   const int h = (int)(rh % Hq);
   const int64_t r = rh / Hq;
-  const int64_t lse_stride = (int64_t)n_q * Hq, o_stride = lse_stride * 32;   // between ranges (float4 of O)
-  const float* pl = part_lse + (int64_t)h * n_q + r;
-  const float4* po = reinterpret_cast<const float4*>(part_o) + t;
-  float4* op = reinterpret_cast<float4*>(o) + ((r + row0) * Hq + h) * 32 + (t & 31);
+  float m = -INFINITY, tot = 0.f;
+  float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (live) {
+    const float* pl = part_lse + (int64_t)h * n_q + r;
+    const float4* po = reinterpret_cast<const float4*>(part_o) + rh * 32 + c;
+    bool nan = false;
+#pragma unroll 4
+    for (int s = g; s < nsplit; s += kGroups) {
+      const float L = pl[s * n];
+      m = fmaxf(m, L);
+      nan |= L != L;
+    }
+    const bool nothing = m == -INFINITY;
+#pragma unroll 4
+    for (int s = g; s < nsplit; s += kGroups) {
+      const float w = nothing ? 1.f : __expf(pl[s * n] - m);   // nothing: the sum of zeros, or the NaN of 0 * inf in V
+      const float4 y = po[s * n * 32];                   // an empty range has stored zeros
+      tot += w;
+      x.x += w * y.x; x.y += w * y.y; x.z += w * y.z; x.w += w * y.w;
+    }
+    if (nan) m = NAN;
+  }
+  xs[team][c] = x;
+  if (c == 0) { ms[team] = m; ts[team] = tot; }
+  __syncthreads();
+  if (!live || g != 0) return;
+  float4* op = reinterpret_cast<float4*>(o) + ((r + row0) * Hq + h) * 32 + c;
   float* lp = lse + (int64_t)h * lse_hs + r + row0;
-  const float la = accumulate ? *lp : -INFINITY;
-  float m = la;
+  const float la = accumulate ? *lp : -INFINITY;         // all lanes of the 32 read it before lane 0 replaces it: they lie in one wavefront
+  m = la;
   bool nan = false;
-  for (int s = 0; s < nsplit; ++s) {
-    const float L = pl[s * lse_stride];
+  for (int k = 0; k < kGroups; ++k) {
+    const float L = ms[team + k];
     m = fmaxf(m, L);
     nan |= L != L;
   }
   if (nan) {                                             // as a workgroup that has all keys leaves such a row
     if (accumulate && la == -INFINITY) return;
     *op = make_float4(NAN, NAN, NAN, NAN);
-    if ((t & 31) == 0 && !accumulate) *lp = -INFINITY;
+    if (c == 0 && !accumulate) *lp = -INFINITY;
     return;
   }
   const bool nothing = m == -INFINITY;
   if (nothing && accumulate) return;                     // both empty: leave the running state
-  float tot = 0.f;
-  float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+  tot = 0.f;
+  x = make_float4(0.f, 0.f, 0.f, 0.f);
   if (accumulate) {
     const float w = __expf(la - m);                      // exp(-inf) = 0
     const float4 y = *op;
     tot = w;
     x.x = w * y.x; x.y = w * y.y; x.z = w * y.z; x.w = w * y.w;
   }
-#pragma unroll 4
-  for (int s = 0; s < nsplit; ++s) {
-    const float w = nothing ? 1.f : __expf(pl[s * lse_stride] - m);   // nothing: the sum of zeros, or the NaN of 0 * inf in V
-    const float4 y = po[s * o_stride];                   // an empty range has stored zeros
-    tot += w;
+  for (int k = 0; k < kGroups; ++k) {
+    const float w = nothing ? 1.f : __expf(ms[team + k] - m);
+    const float4 y = xs[team + k][c];
+    tot += w * ts[team + k];
     x.x += w * y.x; x.y += w * y.y; x.z += w * y.z; x.w += w * y.w;
   }
   const float inv = nothing ? 1.f : 1.f / tot;
   x.x *= inv; x.y *= inv; x.z *= inv; x.w *= inv;
   *op = x;
-  if ((t & 31) == 0) *lp = nothing ? -INFINITY : m + __logf(tot);
+  if (c == 0) *lp = nothing ? -INFINITY : m + __logf(tot);
 }
 
 // dq[rows of the block] += sum of the partial results
@@ -116,40 +142,47 @@ int32_t may_rank(const StepArgs& a, int n_tiles, int n_blocks, int heads_per_til
   return heads_per_tile * mean_document(a) >= (heads_per_tile > 1 ? 200. : 400.) + rounds * n_tiles;
 }
 
-// Only grids smaller than the chip are cut.  The count minimises an estimate in units of one workgroup's
-// time for a 64-key tile (2 us): rounds of workgroups x (tiles of a range + kStart to load Q and the first
-// tiles and to store the result) + the combining pass (a launch, and every partial result written and read
-// at about 4 TB/s = 8 MB per unit).
+// How a grid smaller than the chip is spread over it: by workgroups of 4 instead of 8 wavefronts (twice as many, each with half of
+// the rows and the SIMDs to itself: 64 keys take 0.89 us instead of 1.2) and by cutting the keys into ranges.  Taken is what
+// minimises an estimate in units of 8 wavefronts' time for a tile of 64 keys: rounds of workgroups x (tiles of a range x
+// tile time + the time to load Q and the first tiles and to store the result) + the combining pass (a launch, and every partial result
+// written and read at about 4 TB/s = 5 MB per unit).  Measured, 32 rows of 28/4 heads
+// on 8192 keys, uncut: 162 us with 8 wavefronts, 122 with 4; from 129 workgroups of 8 on a second round of smaller ones costs more than they gain.
 // Documents shorten the visible keys by an amount the host does not know; taken are `mean_documents` documents
 // of the mean length (the block's last position / n_docs), see the callers.  A cut that the documents leave with empty ranges
 // costs 5 to 10 us; half of all keys, whatever n_docs, was such a cut for every block of short documents (100 rows on
 // 8192 keys, 28/4 heads, documents of 60..300: forward 16 us uncut, 25 us cut, 14.6 us by this rule, which does not cut).
 // At most bwd_dkdv_partial_bytes() are used, so that a workspace larger than asked for changes no result.
-int pick_key_ranges(const StepArgs& a, int n_blocks, int64_t bytes_per_range, int64_t room, double mean_documents) {
+KeyRanges pick_key_ranges(const StepArgs& a, int64_t bytes_per_range, int64_t room, double mean_documents) {
   room = std::min(room, bwd_dkdv_partial_bytes());
-  constexpr double kStart = 2., kLaunch = 3., kBytesPerUnit = 8e6;
+  constexpr double kTile[2] = {1., .74}, kStart[2] = {5., 4.}, kLaunch = 4., kBytesPerUnit = 5e6;
   constexpr int kMaxRanges = 64;
   const int n_cu = cu_count();
-  if (n_blocks >= n_cu || bytes_per_range <= 0) return 1;
+  const int64_t rows = (int64_t)a.n_q * a.group;        // of one KV head
+  const int64_t blocks[2] = {(rows + 255) / 256 * a.Hkv, (rows + 127) / 128 * a.Hkv};
+  KeyRanges best = {8, 1};
+  if (blocks[0] >= n_cu || bytes_per_range <= 0) return best;
   int64_t keys = a.n_k;
   if (a.mask == 1) keys = std::max<int64_t>(0, std::min<int64_t>(keys, (int64_t)a.q_pos0 + a.n_q - a.k_pos0));
   if (a.cu != nullptr) keys = std::min(keys, (int64_t)(mean_documents * mean_document(a)));
   const double tiles = (double)((keys + 63) / 64);
-  const int most = (int)std::min<int64_t>({kMaxRanges, room / bytes_per_range, (int64_t)(tiles / 4)});
-  int best = 1;
-  double best_cost = tiles + kStart;
-  for (int n = 2; n <= most; ++n) {
-    const int rounds = (n_blocks * n + n_cu - 1) / n_cu;
-    const double cost = rounds * (tiles / n + kStart) + kLaunch + 2. * n * (double)bytes_per_range / kBytesPerUnit;
-    if (cost < best_cost) { best = n; best_cost = cost; }
-  }
+  const int most = std::max(1, (int)std::min<int64_t>({kMaxRanges, room / bytes_per_range, (int64_t)(tiles / 4)}));
+  double best_cost = 1e300;
+  for (int w = 0; w < 2; ++w)
+    for (int n = 1; n <= most; ++n) {
+      const int64_t rounds = (blocks[w] * n + n_cu - 1) / n_cu;
+      const double cost = rounds * (tiles / n * kTile[w] + kStart[w]) + (n > 1 ? kLaunch + 2. * n * (double)bytes_per_range / kBytesPerUnit : 0.);
+      if (cost < best_cost) { best = {w ? 4 : 8, n}; best_cost = cost; }
+    }
   return best;
 }
 
 hipError_t launch_fwd_combine(const StepArgs& a, const float* part_o, const float* part_lse, int nsplit, hipStream_t stream) {
-  const int64_t n = (int64_t)a.n_q * a.Hq * 32;
-  fwd_combine_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(part_o, part_lse, nsplit, a.n_q, a.Hq, a.q_row0, a.o, a.lse,
-                                                                                 a.lse_hs, a.accumulate);
+  const int64_t n = (int64_t)a.n_q * a.Hq;
+  if (nsplit >= 8)
+    fwd_combine_kernel<8><<<dim3((unsigned)n), dim3(256), 0, stream>>>(part_o, part_lse, nsplit, a.n_q, a.Hq, a.q_row0, a.o, a.lse, a.lse_hs, a.accumulate);
+  else
+    fwd_combine_kernel<2><<<dim3((unsigned)((n + 3) / 4)), dim3(256), 0, stream>>>(part_o, part_lse, nsplit, a.n_q, a.Hq, a.q_row0, a.o, a.lse, a.lse_hs, a.accumulate);
   return hipGetLastError();
 }
 
