@@ -32,11 +32,11 @@ constexpr int kBN = 64;            // keys per tile
 
 enum Result { kStore, kMerge, kPartial };
 
-// n_tiles: row tiles per KV head, kWaves * 32 rows of its list each.
+// n_items: work items per KV head, row tiles of kWaves * 32 rows of its list (x nsplit ranges of their keys).
 // kPartial: nsplit workgroups share the key tiles of every query tile, each stores its (O, LSE) in
 // part_o [nsplit][n_q][Hq][128] and part_lse [nsplit][Hq][n_q] for launch_fwd_combine.
 template <int kWaves, Result kResult>
-__global__ __launch_bounds__(512, 2) void fwd_bf16_kernel(StepArgs a, int n_tiles, int xcd_bits, int nsplit, float* part_o,
+__global__ __launch_bounds__(512, 2) void fwd_bf16_kernel(StepArgs a, int n_items, int xcd_bits, int nsplit, float* part_o,
                                                                            float* part_lse) {
   constexpr int kBM = 32 * kWaves;                      // rows per workgroup
   constexpr int kCopies = 16 / kWaves;
@@ -59,15 +59,20 @@ __global__ __launch_bounds__(512, 2) void fwd_bf16_kernel(StepArgs a, int n_tile
   if (xcd_bits >= 0) {                                  // 2^xcd_bits XCDs per KV head
     kvh = (blockIdx.x & 7) >> xcd_bits;
     tile = (blockIdx.x >> 3 << xcd_bits) + (blockIdx.x & ((1 << xcd_bits) - 1));
-    if (tile >= n_tiles) return;
+    if (tile >= n_items) return;
   } else {
     tile = blockIdx.x / a.Hkv;
     kvh = blockIdx.x - tile * a.Hkv;
   }
-  tile = n_tiles - 1 - tile;
-  const int split = kResult == kPartial ? blockIdx.y : 0;
+  tile = n_items - 1 - tile;
+  int split = 0;
+  if (kResult == kPartial) {                                       // an item is a range of a tile's keys
+    const int item = tile;
+    tile = item / nsplit;
+    split = item - tile * nsplit;
+  }
   const CuLocal cu = local_cu(a, reinterpret_cast<int32_t*>(lds + 8192), 64 * kWaves);
-  if (a.rank) {                                         // n_tiles counts whole blocks of kBM query rows: `group` tiles each
+  if (a.rank) {                                         // n_items counts whole blocks of kBM query rows: `group` tiles each
     int block = tile / a.group;
     const int n_blocks = (a.n_q + kBM - 1) / kBM, sub = tile - block * a.group;
     if (worth_ranking(a, cu, a.q_pos0, a.q_pos0 + a.n_q - 1))
@@ -419,22 +424,22 @@ hipError_t launch(StepArgs a, int nsplit, hipStream_t stream) {
   constexpr int kBM = 32 * kWaves;
   const int n_blocks_q = (a.n_q + kBM - 1) / kBM;
   a.rank = may_rank(a, n_blocks_q, n_blocks_q * nsplit * a.Hq, 1, 5);
-  const int n_tiles = a.rank ? n_blocks_q * a.group : (int)(((int64_t)a.n_q * a.group + kBM - 1) / kBM);
-  int xcd_bits = -1, n_blocks = n_tiles * a.Hkv;
+  const int n_items = (a.rank ? n_blocks_q * a.group : (int)(((int64_t)a.n_q * a.group + kBM - 1) / kBM)) * nsplit;
+  int xcd_bits = -1, n_blocks = n_items * a.Hkv;
   if (8 % a.Hkv == 0) {
     xcd_bits = __builtin_ctz(8 / a.Hkv);
-    n_blocks = 8 * ((n_tiles + (1 << xcd_bits) - 1) >> xcd_bits);
+    n_blocks = 8 * ((n_items + (1 << xcd_bits) - 1) >> xcd_bits);
   }
-  const dim3 g(n_blocks, nsplit), b(64 * kWaves);
+  const dim3 g(n_blocks), b(64 * kWaves);
   if (nsplit > 1) {
     float* part_o = reinterpret_cast<float*>(a.ws);
     float* part_lse = part_o + (int64_t)nsplit * a.n_q * a.Hq * 128;
-    fwd_bf16_kernel<kWaves, kPartial><<<g, b, 0, stream>>>(a, n_tiles, xcd_bits, nsplit, part_o, part_lse);
+    fwd_bf16_kernel<kWaves, kPartial><<<g, b, 0, stream>>>(a, n_items, xcd_bits, nsplit, part_o, part_lse);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : launch_fwd_combine(a, part_o, part_lse, nsplit, stream);
   }
-  if (a.accumulate) fwd_bf16_kernel<kWaves, kMerge><<<g, b, 0, stream>>>(a, n_tiles, xcd_bits, 1, nullptr, nullptr);
-  else fwd_bf16_kernel<kWaves, kStore><<<g, b, 0, stream>>>(a, n_tiles, xcd_bits, 1, nullptr, nullptr);
+  if (a.accumulate) fwd_bf16_kernel<kWaves, kMerge><<<g, b, 0, stream>>>(a, n_items, xcd_bits, 1, nullptr, nullptr);
+  else fwd_bf16_kernel<kWaves, kStore><<<g, b, 0, stream>>>(a, n_items, xcd_bits, 1, nullptr, nullptr);
   return hipGetLastError();
 }
 
@@ -444,7 +449,7 @@ hipError_t launch_fwd_bf16(const StepArgs& a, hipStream_t stream) {
   const int n_blocks_q = (a.n_q + 255) / 256;
   // The slowest query tile counts: one tile lies anywhere in a document, of eight one lies late in a long one.
   const double mean_documents = 1. + (n_blocks_q < 8 ? n_blocks_q - 1 : 7) / 7.;
-  const KeyRanges r = pick_key_ranges(a, (int64_t)a.n_q * a.Hq * 129 * sizeof(float), a.ws_bytes, mean_documents);
+  const KeyRanges r = pick_key_ranges(a, 1.2, (int64_t)a.n_q * a.Hq * 129 * sizeof(float), a.ws_bytes, mean_documents);
   return r.waves == 4 ? launch<4>(a, r.count, stream) : launch<8>(a, r.count, stream);
 }
 

@@ -181,8 +181,8 @@ __device__ __forceinline__ int tile_g_tr(int lane, int db) {
 
 // Copies of a tensor's tiles into TileG slots, one wavefront-copy (4 rows) at a time.  A tile's address is
 // wavefront-uniform; the lane's part of the address is the same for every whole tile, and in one that is not
-// whole it stops at the last row (`limit`), so that rows past the end repeat it.  A copy costs four instructions of which
-// one is a vector instruction: with the address of every copy computed from its tile's index in 64 bits a wavefront spent
+// whole it stops at the last row (`limit`), so that rows past the end repeat it.  A copy costs five instructions of which
+// two are vector instructions: with the address of every copy computed from its tile's index in 64 bits a wavefront spent
 // more issue slots on scalar arithmetic than on matrix instructions.
 template <int kCopies>
 struct TileCopier {
@@ -190,7 +190,7 @@ struct TileCopier {
   uint32_t tile_bytes;
   int last, ragged;                                    // last tile to fetch, the one that is not whole (or -1)
   int lds_wave;                                        // start of the wavefront's first copy inside a slot
-  uint32_t off[kCopies], ragged_limit;
+  uint32_t off, copy_bytes, ragged_limit;              // of the wavefront's first copy; from one to its next
   __device__ __forceinline__ void init(int64_t row_stride_elems, int rows, int last_tile, int wave, int lane) {
     const uint32_t row_bytes = (uint32_t)row_stride_elems * 2, chunk = ((lane & 15) ^ ((lane >> 4) << 2)) << 4;
     tile_bytes = 64 * row_bytes;
@@ -198,8 +198,8 @@ struct TileCopier {
     ragged = rows % 64 != 0 ? rows / 64 : -1;
     lds_wave = __builtin_amdgcn_readfirstlane(wave) * kGroupPitch;
     ragged_limit = (ragged >= 0 ? rows % 64 - 1 : 63) * row_bytes + chunk;
-#pragma unroll
-    for (int i = 0; i < kCopies; ++i) off[i] = (4 * (wave + i * W) + (lane >> 4)) * row_bytes + chunk;
+    off = (4 * wave + (lane >> 4)) * row_bytes + chunk;
+    copy_bytes = 4 * W * row_bytes;
   }
   struct Tile { const char* base; uint32_t limit; };
   // tile t of the tensor whose tile 0 starts at `first`; past the last tile that one again
@@ -209,11 +209,11 @@ struct TileCopier {
   }
   // the wavefront's copy i of a tile into the slot at byte kSlot of the kernel's LDS array (which starts at LDS address 0)
   __device__ __forceinline__ void copy(const Tile& x, int i, int slot_offset) const {
-    const uint32_t o = min(off[i], x.limit);
+    const uint32_t o = min(off + i * copy_bytes, x.limit);
     asm volatile("s_add_i32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_wave), "v"(o), "s"(x.base), "i"(slot_offset + i * W * kGroupPitch) : "memory", "scc");
   }
   __device__ __forceinline__ void copy_to(const Tile& x, int i, int slot_offset) const {   // the same, slot known at run time only
-    const uint32_t o = min(off[i], x.limit);
+    const uint32_t o = min(off + i * copy_bytes, x.limit);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_wave + slot_offset + i * W * kGroupPitch), "v"(o), "s"(x.base) : "memory");
   }
 };

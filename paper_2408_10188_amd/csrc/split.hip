@@ -143,19 +143,20 @@ int32_t may_rank(const StepArgs& a, int n_tiles, int n_blocks, int heads_per_til
 }
 
 // How a grid smaller than the chip is spread over it: by workgroups of 4 instead of 8 wavefronts (twice as many, each with half of
-// the rows and the SIMDs to itself: 64 keys take 0.89 us instead of 1.2) and by cutting the keys into ranges.  Taken is what
-// minimises an estimate in units of 8 wavefronts' time for a tile of 64 keys: rounds of workgroups x (tiles of a range x
+// the rows and the SIMDs to itself: 64 keys take 0.89 us instead of 1.2 in the forward, 1.15 instead of 1.6 in the dQ kernel) and by
+// cutting the keys into ranges.  Taken is what minimises an estimate in us: rounds of workgroups x (tiles of a range x
 // tile time + the time to load Q and the first tiles and to store the result) + the combining pass (a launch, and every partial result
-// written and read at about 4 TB/s = 5 MB per unit).  Measured, 32 rows of 28/4 heads
+// written and read at about 4 TB/s).  Measured, 32 rows of 28/4 heads
 // on 8192 keys, uncut: 162 us with 8 wavefronts, 122 with 4; from 129 workgroups of 8 on a second round of smaller ones costs more than they gain.
 // Documents shorten the visible keys by an amount the host does not know; taken are `mean_documents` documents
 // of the mean length (the block's last position / n_docs), see the callers.  A cut that the documents leave with empty ranges
 // costs 5 to 10 us; half of all keys, whatever n_docs, was such a cut for every block of short documents (100 rows on
 // 8192 keys, 28/4 heads, documents of 60..300: forward 16 us uncut, 25 us cut, 14.6 us by this rule, which does not cut).
 // At most bwd_dkdv_partial_bytes() are used, so that a workspace larger than asked for changes no result.
-KeyRanges pick_key_ranges(const StepArgs& a, int64_t bytes_per_range, int64_t room, double mean_documents) {
+KeyRanges pick_key_ranges(const StepArgs& a, double tile_us, int64_t bytes_per_range, int64_t room, double mean_documents) {
   room = std::min(room, bwd_dkdv_partial_bytes());
-  constexpr double kTile[2] = {1., .74}, kStart[2] = {5., 4.}, kLaunch = 4., kBytesPerUnit = 5e6;
+  const double tile[2] = {tile_us, .73 * tile_us};
+  constexpr double kStart[2] = {6., 5.}, kLaunch = 5., kBytesPerUs = 4.2e6;
   constexpr int kMaxRanges = 64;
   const int n_cu = cu_count();
   const int64_t rows = (int64_t)a.n_q * a.group;        // of one KV head
@@ -171,7 +172,7 @@ KeyRanges pick_key_ranges(const StepArgs& a, int64_t bytes_per_range, int64_t ro
   for (int w = 0; w < 2; ++w)
     for (int n = 1; n <= most; ++n) {
       const int64_t rounds = (blocks[w] * n + n_cu - 1) / n_cu;
-      const double cost = rounds * (tiles / n * kTile[w] + kStart[w]) + (n > 1 ? kLaunch + 2. * n * (double)bytes_per_range / kBytesPerUnit : 0.);
+      const double cost = rounds * (tiles / n * tile[w] + kStart[w]) + (n > 1 ? kLaunch + 2. * n * (double)bytes_per_range / kBytesPerUs : 0.);
       if (cost < best_cost) { best = {w ? 4 : 8, n}; best_cost = cost; }
     }
   return best;

@@ -1,4 +1,4 @@
-"""Forward and backward steps at the edges of the forward's tiles, against the fp64 oracle.  The rows of the heads that share
+"""Forward and backward steps at the edges of the forward's and the dQ kernel's tiles, against the fp64 oracle.  The rows of the heads that share
 a KV head are one list cut into tiles of 128 or 256 (row, head) pairs, so an edge can fall between two heads of a row;
 the key loop takes four tiles of 64 per trip and starts in the middle of one."""
 import pytest
