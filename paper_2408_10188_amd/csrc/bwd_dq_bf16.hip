@@ -335,23 +335,29 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_i
     iteration(std::integral_constant<int, 2>(), t + 2);
     iteration(std::integral_constant<int, 3>(), t + 3);
   }
-  __builtin_amdgcn_s_waitcnt(0x0F70);                    // drain the copies issued past the end
-
-  // where the result goes, computed anew: kept from above it would take registers that the loop is short of
-  const int lane_e = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), row_e = tile_row0 + wave_s * 32 + (lane_e & 31);
-  if (row_e >= n_rows) return;
-  const int q_row_e = row_of_pair(a, row_e), h_e = kvh * a.group + row_e - q_row_e * a.group;
-  float* out = (kPartial ? part + ((int64_t)split * a.n_q + q_row_e) * a.Hq * 128 : a.dq + (int64_t)(a.q_row0 + q_row_e) * a.Hq * 128) + h_e * 128 + (lane_e >> 5) * 4;
+  __builtin_amdgcn_s_waitcnt(0x0F70);                   // the copies issued past the end have landed, everybody is done with the tiles:
+  lds_barrier();                                        // the result can pass through LDS
+  // lane, half and column anew: kept from above they would take registers that the loop is short of
+  const int lane_e = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), half_e = lane_e >> 5, col_e = lane_e & 31;
+  float* const out = kPartial ? part + (int64_t)split * a.n_q * a.Hq * 128 : a.dq + (int64_t)a.q_row0 * a.Hq * 128;
+  auto result_at = [&](int list_row) {                   // where this lane's 16 bytes of a row of the list go
+    return reinterpret_cast<float4*>(out + ((int64_t)row_of_pair(a, list_row) * (a.Hq - a.group) + kvh * a.group + list_row) * 128) + col_e;
+  };
+  const int row_up = tile_row0 + wave_s * 32 + half_e;   // this half of the wavefront takes every other row from here on
+  float4 old[16];
+  if (!kPartial) {                                       // all sixteen on their way before anything waits
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
+    for (int i = 0; i < 16; ++i)
+      if (row_up + 2 * i < n_rows) old[i] = *result_at(row_up + 2 * i);
+  }
+  char* const area = lds + wave_s * kResultBytes;
+  result_to_lds(area, dq, a.scale, half_e, col_e);
 #pragma unroll
-    for (int g4 = 0; g4 < 4; ++g4) {
-      float4* dst = reinterpret_cast<float4*>(out + db * 32 + g4 * 8);
-      float4 o = kPartial ? make_float4(0.f, 0.f, 0.f, 0.f) : *dst;
-      o.x += a.scale * dq[db][g4 * 4 + 0]; o.y += a.scale * dq[db][g4 * 4 + 1];
-      o.z += a.scale * dq[db][g4 * 4 + 2]; o.w += a.scale * dq[db][g4 * 4 + 3];
-      *dst = o;
-    }
+  for (int i = 0; i < 16; ++i) {
+    float4 o = result_chunk(area, 2 * i + half_e, col_e);
+    if (!kPartial) { o.x += old[i].x; o.y += old[i].y; o.z += old[i].z; o.w += old[i].w; }
+    if (row_up + 2 * i < n_rows) *result_at(row_up + 2 * i) = o;
+  }
 }
 
 template <int kWaves>

@@ -373,8 +373,9 @@ __global__ __launch_bounds__(512, 2) void fwd_bf16_kernel(StepArgs a, int n_item
         if (n + kDepth < 16) op[n % kDepth] = read_v(n + kDepth, 3);
       }
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);                 // drain the copies issued past the end before the workgroup leaves
   }
+  __builtin_amdgcn_s_waitcnt(0x0F70);                   // the copies issued past the end have landed, everybody is done with the tiles:
+  lds_barrier();                                        // the result can pass through LDS
   const float m = m_ref;
 
   // ---- epilogue ----
@@ -383,36 +384,49 @@ __global__ __launch_bounds__(512, 2) void fwd_bf16_kernel(StepArgs a, int n_item
   const float inv = empty ? 0.f : 1.f / l;
   // A row of NaNs reports LSE = -inf, a range's share of one NaN: the combining pass has to tell it from an empty range.
   const float lse_part = (kResult == kPartial ? l == 0.f : empty) ? -INFINITY : (m * c + __builtin_amdgcn_logf(l)) * kLn2;   // v_log_f32 is log2
-  if (!live) return;
-  const int64_t r = a.q_row0 + q_row;
-  float* op_ = (kResult == kPartial ? part_o + ((int64_t)split * a.n_q + q_row) * a.Hq * 128 : a.o + r * a.Hq * 128) + h * 128 + half * 4;
-  float* lp = kResult == kPartial ? part_lse + ((int64_t)split * a.Hq + h) * a.n_q + q_row : a.lse + (int64_t)h * a.lse_hs + r;
-  float wa = 0.f, wb = inv;
-  if (kResult == kMerge) {
-    const float la = *lp;
-    const float mm = fmaxf(la, lse_part);
-    if (mm == -INFINITY) return;                        // both sides empty
-    const float ea = __expf(la - mm), eb = __expf(lse_part - mm);
-    const float tot = ea + eb;
-    wa = ea / tot;
-    wb = eb / tot * inv;
-    if (half == 0) *lp = mm + __logf(tot);
-  } else {
-    if (half == 0) *lp = lse_part;
+  float* const out = kResult == kPartial ? part_o + (int64_t)split * a.n_q * a.Hq * 128 : a.o + (int64_t)a.q_row0 * a.Hq * 128;
+  auto result_at = [&](int list_row) {                   // where this lane's 16 bytes of a row of the list go
+    return reinterpret_cast<float4*>(out + ((int64_t)row_of_pair(a, list_row) * (a.Hq - a.group) + kvh * a.group + list_row) * 128) + col;
+  };
+  const int row_up = tile_row0 + wave * 32 + half;       // this half of the wavefront takes every other row from here on
+  float4 old[16];
+  if (kResult == kMerge) {                               // all sixteen on their way before anything waits
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (row_up + 2 * i < n_rows) old[i] = *result_at(row_up + 2 * i);
   }
-#pragma unroll
-  for (int db = 0; db < 4; ++db)
-#pragma unroll
-    for (int g4 = 0; g4 < 4; ++g4) {
-      float4* dst = reinterpret_cast<float4*>(op_ + db * 32 + g4 * 8);
-      float4 o = make_float4(oacc[db][g4 * 4 + 0] * wb, oacc[db][g4 * 4 + 1] * wb, oacc[db][g4 * 4 + 2] * wb,
-                             oacc[db][g4 * 4 + 3] * wb);
-      if (kResult == kMerge) {
-        const float4 old = *dst;
-        o.x += wa * old.x; o.y += wa * old.y; o.z += wa * old.z; o.w += wa * old.w;
-      }
-      *dst = o;
+  float wa = 0.f, wb = inv;
+  constexpr float kSkip = -1.f;                          // in the place of a weight, which is never negative: leave the row alone
+  if (live) {
+    float* lp = kResult == kPartial ? part_lse + ((int64_t)split * a.Hq + h) * a.n_q + q_row : a.lse + (int64_t)h * a.lse_hs + a.q_row0 + q_row;
+    float lse_new = lse_part;
+    if (kResult == kMerge) {
+      const float la = *lp;
+      const float mm = fmaxf(la, lse_part);
+      const float ea = __expf(la - mm), eb = __expf(lse_part - mm);
+      const float tot = ea + eb;
+      wa = mm == -INFINITY ? kSkip : ea / tot;          // both sides empty: the running result stays
+      wb = eb / tot * inv;
+      lse_new = mm + __logf(tot);
     }
+    if (half == 0 && wa != kSkip) *lp = lse_new;
+  }
+  float* const weights = reinterpret_cast<float*>(lds + kWaves * kResultBytes) + wave * 32;
+  if (kResult == kMerge && half == 0) weights[col] = wa;
+  char* const area = lds + wave * kResultBytes;
+  result_to_lds(area, oacc, wb, half, col);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int rr = 2 * i + half;
+    float4 o = result_chunk(area, rr, col);
+    bool on = row_up + 2 * i < n_rows;
+    if (kResult == kMerge) {
+      const float w = weights[rr];
+      on = on && w != kSkip;
+      o.x += w * old[i].x; o.y += w * old[i].y; o.z += w * old[i].z; o.w += w * old[i].w;
+    }
+    if (on) *result_at(row_up + 2 * i) = o;
+  }
 }
 
 }  // namespace

@@ -218,4 +218,23 @@ struct TileCopier {
   }
 };
 
+// ---------------------------------------------------------------------------------------
+// Results leave through LDS.  A lane of a transposed accumulator (acc[db][i]: d = 32 db + 8 (i / 4) + 4 half + i % 4 of row
+// `col`) holds 16 bytes here and there of one row, and a store of them touches 32 rows at once, 32 bytes each; read back
+// row by row a store (and the read of what it is added to) takes two whole rows of 512 bytes.  16 KiB per wavefront, chunk c of
+// row r at position c ^ r of its row.  The caller sees to it that nobody uses the area any more.
+// ---------------------------------------------------------------------------------------
+constexpr int kResultBytes = 32 * 512;
+__device__ __forceinline__ void result_to_lds(char* area, const f32x16 (&acc)[4], float mul, int half, int col) {
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4)
+      *reinterpret_cast<float4*>(area + col * 512 + (((db * 8 + g4 * 2 + half) ^ col) << 4)) =
+          make_float4(acc[db][g4 * 4 + 0] * mul, acc[db][g4 * 4 + 1] * mul, acc[db][g4 * 4 + 2] * mul, acc[db][g4 * 4 + 3] * mul);
+}
+__device__ __forceinline__ float4 result_chunk(const char* area, int row, int c) {
+  return *reinterpret_cast<const float4*>(area + row * 512 + ((c ^ row) << 4));
+}
+
 }  // namespace mmsp
