@@ -224,11 +224,11 @@ __global__ __launch_bounds__(64 * kWaves) void fwd_f32_kernel(StepArgs a) {
   }
 }
 
+// dQ of 16 query rows of one head; parts: kWaves * kPartFloats<D> floats
 template <int D>
-__global__ __launch_bounds__(64 * kWaves) void bwd_dq_f32_kernel(StepArgs a) {
-  __shared__ __attribute__((aligned(16))) float parts[kWaves * kPartFloats<D>];
+__device__ __forceinline__ void dq_rows(const StepArgs& a, float* parts, int row_block, int h) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, col = lane & 15;
-  const int row0 = blockIdx.x * kRows, h = blockIdx.y, kvh = h / a.group;
+  const int row0 = row_block * kRows, kvh = h / a.group;
   const int rowc = min(row0 + col, a.n_q - 1);
   int lo, hi;
   key_interval_of_row(a, CuGlobal{a.cu}, rowc, lo, hi);
@@ -282,12 +282,12 @@ __global__ __launch_bounds__(64 * kWaves) void bwd_dq_f32_kernel(StepArgs a) {
   }
 }
 
-// 16 keys of one KV head per workgroup; the wavefronts share out the (head of the group, query block) sequence.
+// dK and dV of 16 keys of one KV head; the wavefronts share out the (head of the group, query block) sequence.
+// parts: 2 kWaves * kPartFloats<D> floats
 template <int D>
-__global__ __launch_bounds__(64 * kWaves) void bwd_dkdv_f32_kernel(StepArgs a) {
-  __shared__ __attribute__((aligned(16))) float parts[2 * kWaves * kPartFloats<D>];
+__device__ __forceinline__ void dkdv_keys(const StepArgs& a, float* parts, int key_block, int kvh) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, col = lane & 15;
-  const int key0 = blockIdx.x * kRows, kvh = blockIdx.y;
+  const int key0 = key_block * kRows;
   const int keyc = min(key0 + col, a.n_k - 1);
   int lo, hi;
   row_interval_of_key(a, CuGlobal{a.cu}, keyc, lo, hi);
@@ -362,6 +362,32 @@ __global__ __launch_bounds__(64 * kWaves) void bwd_dkdv_f32_kernel(StepArgs a) {
   }
 }
 
+// The first n_dkdv workgroups take key blocks (the longer chains), the others query blocks: both gradients need only what
+// the forward left, so one launch serves both where the chip has room for all of them at once.
+template <int D, bool kDkdv>
+__global__ __launch_bounds__(64 * kWaves) void bwd_f32_kernel(StepArgs a, int n_dkdv) {
+  __shared__ __attribute__((aligned(16))) float parts[(kDkdv ? 2 : 1) * kWaves * kPartFloats<D>];
+  const int b = blockIdx.x, kb = (a.n_k + kRows - 1) / kRows, qb = (a.n_q + kRows - 1) / kRows;
+  if (kDkdv && b < n_dkdv) dkdv_keys<D>(a, parts, b % kb, b / kb);
+  else dq_rows<D>(a, parts, (b - n_dkdv) % qb, (b - n_dkdv) / qb);
+}
+
+template <int D>
+hipError_t launch_bwd(const StepArgs& a, hipStream_t stream) {
+  const int64_t n_dq = a.dq != nullptr ? (int64_t)((a.n_q + kRows - 1) / kRows) * a.Hq : 0;
+  const int64_t n_dkdv = a.dk != nullptr ? (int64_t)((a.n_k + kRows - 1) / kRows) * a.Hkv : 0;
+  const dim3 b(64 * kWaves);
+  // A step of 256 rows and two heads: 20 us + 10 us as two launches, 20 us as one.  With more workgroups than CUs
+  // two launches, because a CU holds two of the smaller dQ workgroups.
+  if (n_dq > 0 && n_dkdv > 0 && n_dq + n_dkdv <= cu_count()) {
+    bwd_f32_kernel<D, true><<<dim3((unsigned)(n_dq + n_dkdv)), b, 0, stream>>>(a, (int)n_dkdv);
+    return hipGetLastError();
+  }
+  if (n_dq > 0) bwd_f32_kernel<D, false><<<dim3((unsigned)n_dq), b, 0, stream>>>(a, 0);
+  if (n_dkdv > 0) bwd_f32_kernel<D, true><<<dim3((unsigned)n_dkdv), b, 0, stream>>>(a, (int)n_dkdv);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_fwd_f32(const StepArgs& a, hipStream_t stream) {
@@ -371,16 +397,6 @@ hipError_t launch_fwd_f32(const StepArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_f32(const StepArgs& a, hipStream_t stream) {
-  const dim3 gq((a.n_q + kRows - 1) / kRows, a.Hq), gk((a.n_k + kRows - 1) / kRows, a.Hkv), b(64 * kWaves);
-  if (a.d == 64) {
-    if (a.dq != nullptr) bwd_dq_f32_kernel<64><<<gq, b, 0, stream>>>(a);
-    if (a.dk != nullptr) bwd_dkdv_f32_kernel<64><<<gk, b, 0, stream>>>(a);
-  } else {
-    if (a.dq != nullptr) bwd_dq_f32_kernel<128><<<gq, b, 0, stream>>>(a);
-    if (a.dk != nullptr) bwd_dkdv_f32_kernel<128><<<gk, b, 0, stream>>>(a);
-  }
-  return hipGetLastError();
-}
+hipError_t launch_bwd_f32(const StepArgs& a, hipStream_t stream) { return a.d == 64 ? launch_bwd<64>(a, stream) : launch_bwd<128>(a, stream); }
 
 }  // namespace mmsp
