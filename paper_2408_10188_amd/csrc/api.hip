@@ -84,7 +84,9 @@ mmsp::StepArgs make_args(const mmsp_shape* s, const mmsp_block* b) {
   a.lse_hs = s->lse_head_stride; a.scale = s->softmax_scale;
   a.q_row0 = (int32_t)b->q_row0; a.n_q = (int32_t)b->n_q; a.k_row0 = (int32_t)b->k_row0; a.n_k = (int32_t)b->n_k;
   a.q_pos0 = (int32_t)b->q_pos0; a.k_pos0 = (int32_t)b->k_pos0;
-  a.mask = b->mask; a.n_docs = b->n_docs; a.cu = b->cu_seqlens;
+  a.mask = b->mask;
+  if (a.mask == MMSP_MASK_CAUSAL_DIAG && b->q_pos0 >= b->k_pos0 + b->n_k - 1) a.mask = MMSP_MASK_FULL;   // no key follows the first query
+  a.n_docs = b->n_docs; a.cu = b->cu_seqlens;
   return a;
 }
 

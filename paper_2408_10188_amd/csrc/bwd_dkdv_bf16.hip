@@ -19,6 +19,9 @@
 // software-pipelined over blocks: while the pipe computes S and dP of block b+1 the vector units
 // turn dP of block b into dS; while it accumulates dV and dK of block b they take the exponentials
 // of block b+1.  The operand of every matrix instruction is read from LDS four instructions ahead.
+#include <algorithm>
+#include <cmath>
+
 #include "mfma_tiles.h"
 
 namespace mmsp {
@@ -104,14 +107,12 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
     kt = heaviest_first(kt, n_kt, 64 * kWaves, reinterpret_cast<int*>(lds), [&](int i) { return query_tiles_of_keys(a, cu, i * kKeys, kKeys); });
   const int tile_key0 = kt * kKeys;
   const int key = tile_key0 + wave * 32 + col;           // block-relative key of this lane
-  const bool live = key < a.n_k;
-  const int keyc = min(key, a.n_k - 1);
+  const int keyc = min(key, a.n_k - 1);                  // a lane past the end repeats the last key: a column of its own that nobody stores
 
   int rlo, rhi;                                          // query rows that see this lane's key
   row_interval_of_key(a, cu, keyc, rlo, rhi);
-  const int w_hi_min = __builtin_amdgcn_readlane(rhi, 0);
-  if (!live) { rlo = a.n_q; rhi = a.n_q - 1; }
-  const int w_lo_max = __builtin_amdgcn_readlane(rlo, 31);   // last key of the wavefront (n_q for a dead key: always mask)
+  const int w_hi_min = __builtin_amdgcn_readlane(rhi, 0);    // first and last key of the wavefront
+  const int w_lo_max = __builtin_amdgcn_readlane(rlo, 31);
   int t_lo, t_hi, dummy;
   row_interval_of_key(a, cu, tile_key0, t_lo, dummy);
   row_interval_of_key(a, cu, min(tile_key0 + kKeys, a.n_k) - 1, dummy, t_hi);
@@ -134,20 +135,6 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
   }
   if (niter == 0 && nsplit == 1 && a.accumulate) return;   // nothing visible, nothing to add
 
-  // K and V rows of this lane's key as B operands (k index along d)
-  u32x4 kreg[8], vreg[8];
-  {
-    const int64_t off = (int64_t)(a.k_row0 + keyc) * a.kv_ts + (int64_t)kvh * a.kv_hs + half * 8;
-    const uint16_t* pk = reinterpret_cast<const uint16_t*>(a.k) + off;
-    const uint16_t* pv = reinterpret_cast<const uint16_t*>(a.v) + off;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      kreg[ks] = *reinterpret_cast<const u32x4*>(pk + ks * 16);
-      vreg[ks] = *reinterpret_cast<const u32x4*>(pv + ks * 16);
-    }
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) { MMSP_PIN_ACC(kreg[ks]); MMSP_PIN_ACC(vreg[ks]); }   // landed before the tile copies are counted; AGPRs
-  }
   const float c = a.scale * kLog2e;
 
   f32x16 dv[4], dk[4];                                   // dV^T, dK^T: 128 d x 32 keys
@@ -211,6 +198,20 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
       for (int piece = 0; piece < kGroup; ++piece) fetch_piece(f, piece, qdst, odst, sdst);
     };
     fetch(qs0, os0, st0);
+    // K and V rows of this lane's key as B operands (k index along d), on their way together with the first tile
+    u32x4 kreg[8], vreg[8];
+    {
+      const int64_t off = (int64_t)(a.k_row0 + keyc) * a.kv_ts + (int64_t)kvh * a.kv_hs + half * 8;
+      const uint16_t* pk = reinterpret_cast<const uint16_t*>(a.k) + off;
+      const uint16_t* pv = reinterpret_cast<const uint16_t*>(a.v) + off;
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) {
+        kreg[ks] = *reinterpret_cast<const u32x4*>(pk + ks * 16);
+        vreg[ks] = *reinterpret_cast<const u32x4*>(pv + ks * 16);
+      }
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) { MMSP_PIN_ACC(kreg[ks]); MMSP_PIN_ACC(vreg[ks]); }   // landed before the other tiles' copies are counted; AGPRs
+    }
     fetch(qs1, os1, st1);
     fetch(qs2, os2, st2);
 
@@ -435,42 +436,31 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
     __builtin_amdgcn_s_waitcnt(0x0F70);                  // drain the copies issued past the end before the workgroup leaves
   }
 
-  if (!live) return;
-  if (nsplit > 1) {                                      // partial result of this range, summed by dkdv_reduce_kernel
-    const int64_t slot_elems = (int64_t)n_kt * kKeys * a.Hkv * 128;
-#pragma unroll
-    for (int which = 0; which < 2; ++which) {
-      const float mul = which ? 1.f : a.scale;
-      float* out = w.partial + ((int64_t)(which ? nsplit : 0) + split) * slot_elems + ((int64_t)key * a.Hkv + kvh) * 128 + half * 4;
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          const f32x16& x = which ? dv[db] : dk[db];
-          *reinterpret_cast<float4*>(out + db * 32 + g4 * 8) =
-              make_float4(mul * x[g4 * 4 + 0], mul * x[g4 * 4 + 1], mul * x[g4 * 4 + 2], mul * x[g4 * 4 + 3]);
-        }
-    }
-    return;
-  }
-  const int64_t off = ((int64_t)(a.k_row0 + key) * a.Hkv + kvh) * 128 + half * 4;
+  // The results pass through LDS (everybody is done with the tiles, and the copies issued past the end have landed): into the
+  // partial result of this range, summed by dkdv_reduce_kernel, or where they belong.
+  lds_barrier();
+  char* const area = lds + wave * 2 * kResultBytes;
+  result_to_lds(area, dk, a.scale, half, col);
+  result_to_lds(area + kResultBytes, dv, 1.f, half, col);
+  const bool partial = nsplit > 1, add = a.accumulate && !partial;
+  const int64_t slot_elems = (int64_t)n_kt * kKeys * a.Hkv * 128, rows_at = ((int64_t)(partial ? 0 : a.k_row0) * a.Hkv + kvh) * 128;
+  const int key_up = tile_key0 + wave * 32 + half;       // this half of the wavefront takes every other key from here on
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
-    const float mul = which ? 1.f : a.scale;
-    float* out = (which ? a.dv : a.dk) + off;
+    float* const out = (partial ? w.partial + ((int64_t)(which ? nsplit : 0) + split) * slot_elems : which ? a.dv : a.dk) + rows_at;
+    auto result_at = [&](int key) { return reinterpret_cast<float4*>(out + (int64_t)key * a.Hkv * 128) + col; };
+    float4 old[16];
+    if (add) {
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+      for (int i = 0; i < 16; ++i)
+        if (key_up + 2 * i < a.n_k) old[i] = *result_at(key_up + 2 * i);
+    }
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const f32x16& x = which ? dv[db] : dk[db];
-        float4* p = reinterpret_cast<float4*>(out + db * 32 + g4 * 8);
-        float4 y = make_float4(mul * x[g4 * 4 + 0], mul * x[g4 * 4 + 1], mul * x[g4 * 4 + 2], mul * x[g4 * 4 + 3]);
-        if (a.accumulate) {
-          const float4 o = *p;
-          y.x += o.x; y.y += o.y; y.z += o.z; y.w += o.w;
-        }
-        *p = y;
-      }
+    for (int i = 0; i < 16; ++i) {
+      float4 o = result_chunk(area + which * kResultBytes, 2 * i + half, col);
+      if (add) { o.x += old[i].x; o.y += old[i].y; o.z += old[i].z; o.w += old[i].w; }
+      if (key_up + 2 * i < a.n_k) *result_at(key_up + 2 * i) = o;
+    }
   }
 }
 #undef MMSP_PIN
@@ -486,6 +476,7 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restric
   const float* src = partial + (int64_t)blockIdx.y * nsplit * slot_elems + i * 4;
   float4* dst = reinterpret_cast<float4*>(blockIdx.y ? dv : dk) + i;
   float4 x = accumulate ? *dst : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
   for (int sidx = 0; sidx < nsplit; ++sidx) {
     const float4 p = *reinterpret_cast<const float4*>(src + sidx * slot_elems);
     x.x += p.x; x.y += p.y; x.z += p.z; x.w += p.w;
@@ -495,27 +486,45 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restric
 
 }  // namespace
 
-// Workgroups the partial-sum area is sized for: ranges are only cut while (key tiles x KV
-// heads x ranges) stays within this count.
+// The partial-sum area holds this many key tiles' dK and dV.
 constexpr int kSplitMaxBlocks = 512;
-constexpr int kSplitMaxRanges = 8;
+constexpr int kSplitMaxRanges = 32;
 
 int64_t bwd_dkdv_partial_bytes() { return 2LL * kSplitMaxBlocks * kKeys * 128 * (int64_t)sizeof(float); }
+
+// Into how many shares a key tile's (query tile, head) sequence is dealt: what minimises an estimate in us.  A share costs
+// kStart plus t per element (64 rows of one head; less under a mask, where CUs that are done early leave their power to the
+// others); with every pair visible all workgroups carry the same work and come in whole rounds, under a mask the heaviest
+// counts, or the sum over all CUs where that is more (heavy tiles come first).  The reduction costs a launch and one
+// write and one read of every partial result (3.3 TB/s measured).  Measured, us with 1 / 2 / 3 / 4 / 5 / 6 / 8 / 12 shares:
+//   28/4 heads, 760 x 1520:          156  93  71  62  56  77  69 156 (5 are 240 workgroups; 12 do not fit)
+//   8/8 heads, 320 x 640:             18  22  24  25  27  29  36  38
+//   7/1 heads, 2560 x 2560 causal:   350 189 134 105  88  78  66  54
+//   4/2 heads, 50 rows behind 8000:   16  31  35  44 (before this estimate: as many as fill the chip, at most 8)
+static int pick_shares(const StepArgs& a, int n_kt) {
+  const double n_cu = cu_count(), base = (double)n_kt * a.Hkv, slot_bytes = 2. * kKeys * 128 * sizeof(float) * base;
+  const bool even = a.mask == 0 && a.cu == nullptr;
+  double most = (double)tiles_of(a.n_q) * a.group;      // elements of the heaviest key tile
+  if (a.cu != nullptr) most = std::min(most, (2. * mean_document(a) / kBQ + 1.) * a.group);
+  const double t = even ? 1.75 : 1.4, mean = even ? most : .5 * most;
+  constexpr double kStart = 6., kLaunch = 4., kBytesPerUs = 3.3e6;
+  const int limit = (int)std::min({(double)kSplitMaxRanges, (double)bwd_dkdv_partial_bytes() / slot_bytes, most});
+  int best = 1;
+  double best_cost = 1e300;
+  for (int n = 1; n == 1 || n <= limit; ++n) {
+    const double share = std::ceil(most / n) * t + kStart, blocks = base * n;
+    const double kernel = even ? std::ceil(blocks / n_cu) * share : std::max(share, 1.1 * (base * mean * t + blocks * kStart) / n_cu);
+    const double cost = kernel + (n > 1 ? kLaunch + n * slot_bytes / kBytesPerUs : 0.);
+    if (cost < best_cost) { best = n; best_cost = cost; }
+  }
+  return best;
+}
 
 hipError_t launch_bwd_dkdv_bf16(const StepArgs& args, const BwdWorkspace& w, hipStream_t stream) {
   StepArgs a = args;
   const int n_kt = (a.n_k + kKeys - 1) / kKeys;
-  // One workgroup per (key tile, KV head) fills the chip only if there are about as many as
-  // CUs; with fewer, cut every key tile's query sequence into ranges.
-  const int n_cu = cu_count();
-  // With every pair visible all key tiles carry the same work and one round of workgroups is
-  // best; under a mask the work per key tile varies (by 2x across a causal block), so aim for
-  // two rounds of shorter workgroups, which the dispatcher then balances (heavy tiles come first).
   const bool no_mask = a.mask == 0 && a.cu == nullptr && a.n_q % kBQ == 0;
-  const int base_blocks = n_kt * a.Hkv;
-  const int target = min(no_mask ? n_cu : 2 * n_cu, kSplitMaxBlocks);
-  int nsplit = min(target / base_blocks, kSplitMaxRanges);
-  if (nsplit < 2) nsplit = 1;
+  const int nsplit = pick_shares(a, n_kt);
   const int n_items = n_kt * nsplit;
   a.rank = may_rank(a, n_kt, n_items * a.Hkv, a.group, 7);
   int xcd_per_kv = 0, n_blocks = n_items * a.Hkv;

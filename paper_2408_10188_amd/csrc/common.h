@@ -191,6 +191,7 @@ hipError_t launch_bwd_stats(const float* lse, const float* delta, int64_t lse_hs
 
 // Query tiles whose key range is cut into several workgroups (forward, dQ), see split.hip.
 int cu_count();
+double mean_document(const StepArgs& a);
 int32_t may_rank(const StepArgs& a, int n_tiles, int n_blocks, int heads_per_tile, int max_rounds);
 struct KeyRanges { int waves, count; };                 // wavefronts of a workgroup, workgroups that share a tile's keys
 KeyRanges pick_key_ranges(const StepArgs& a, double tile_us, int64_t bytes_per_range, int64_t room, double mean_documents);

@@ -122,7 +122,7 @@ int cu_count() {
 
 // Mean length of the documents up to the block's last position: exact for a whole sequence, too short for its earlier
 // parts (n_docs counts the later documents too).
-static double mean_document(const StepArgs& a) {
+double mean_document(const StepArgs& a) {
   return (double)std::max(0, std::max(a.q_pos0 + a.n_q, a.k_pos0 + a.n_k)) / a.n_docs;
 }
 

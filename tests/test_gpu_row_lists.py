@@ -27,3 +27,19 @@ def test_tiles_of_the_row_list(hq, hkv, n_q, n_k):
 def test_documents_shorter_than_a_tile(hq, hkv, cu):
     for mask in (B.MMSP_MASK_FULL, B.MMSP_MASK_CAUSAL_DIAG):
         _run_step(True, hq, hkv, 128, 330, 330, dict(q_row0=0, n_q=330, k_row0=0, n_k=330, mask=mask, q_pos0=0, k_pos0=0), cu=cu, seed=len(cu))
+
+
+@pytest.mark.parametrize("hq,hkv,n_q,n_k,mask,pos", [
+    (7, 1, 1300, 130, B.MMSP_MASK_FULL, 0),                  # 147 elements a key tile, dealt to some twenty workgroups
+    (7, 1, 1100, 1100, B.MMSP_MASK_CAUSAL_DIAG, 0),
+    (5, 5, 70, 900, B.MMSP_MASK_CAUSAL_DIAG, 830),           # two elements: not dealt out
+    (4, 2, 200, 129, B.MMSP_MASK_CAUSAL_DIAG, -20),          # one live key in the last tile, rows that see nothing
+])
+def test_shares_of_a_key_tile(hq, hkv, n_q, n_k, mask, pos):
+    _run_step(True, hq, hkv, 128, n_q + 1, n_k + 2, dict(q_row0=1, n_q=n_q, k_row0=2, n_k=n_k, mask=mask, q_pos0=pos, k_pos0=0), seed=n_q)
+
+
+@pytest.mark.parametrize("q_pos0", [98, 99, 100, 5000])
+def test_a_causal_mask_that_hides_nothing(q_pos0):
+    """From q_pos0 = 99 on no key of 0..99 follows the first query: such a block runs as one without a mask."""
+    _run_step(True, 6, 2, 128, 64, 100, dict(q_row0=0, n_q=64, k_row0=0, n_k=100, mask=B.MMSP_MASK_CAUSAL_DIAG, q_pos0=q_pos0, k_pos0=0), seed=q_pos0)
