@@ -54,6 +54,28 @@ def _fork(side):
     return main
 
 
+def _ptr(t):
+    """Address of a tensor's data (or None): taken once per pass, not once per call."""
+    return t.data_ptr() if hasattr(t, "data_ptr") else t
+
+
+def _block_ptrs(x, n):
+    """Addresses of x[0] .. x[n-1].  Indexing a tensor makes a new one each time, which took longer than the call it was
+    made for: a step of a small ring waited for the host."""
+    if not hasattr(x, "data_ptr"):
+        return [_ptr(x[r]) for r in range(n)]
+    if x.shape[0] < n:
+        raise IndexError("%d blocks given, %d needed" % (x.shape[0], n))
+    base, step = x.data_ptr(), x.stride(0) * x.element_size()
+    return [base + r * step for r in range(n)]
+
+
+def _fill_rows(shape, row0, n_rows, q, k, v, o, lse, ws, ws_bytes, stream):
+    """An empty result for rows that no step reaches."""
+    if n_rows > 0:
+        B.mmsp_attn_step_fwd(shape, B.make_block(row0, n_rows, 0, 0, B.MMSP_MASK_NONE, 0, 0), q, k, v, o, lse, False, ws, ws_bytes, stream)
+
+
 def rank_forward(shape, T, N, rank, q, k_zz, v_zz, o_acc, lse, o_final=None, stream=0, fused_merge=True,
                  o_part=None, lse_part=None, ws=None, ws_bytes=0, side=None, plan=None):
     """All N forward steps of `rank`.  fused_merge=True merges in the step kernel's epilogue;
@@ -64,21 +86,24 @@ def rank_forward(shape, T, N, rank, q, k_zz, v_zz, o_acc, lse, o_final=None, str
     mmsp_contiguous_plan, q and k_zz[r] hold the contiguous chunk r instead of the zigzag pair."""
     n_rows = q.shape[0]
     plan = plan or B.mmsp_zigzag_plan
+    k_zz, v_zz = _block_ptrs(k_zz, N), _block_ptrs(v_zz, N)
+    q, o_acc, lse, ws = _ptr(q), _ptr(o_acc), _ptr(lse), _ptr(ws)
     if side is not None and N > 1:
         main = _fork(side)
-        # rows that no odd step reaches must still hold an empty partial result
-        B.mmsp_attn_step_fwd(shape, B.make_block(0, n_rows, 0, 0, B.MMSP_MASK_NONE, 0, 0), q, k_zz[0], v_zz[0],
-                             side.o_acc, side.lse, False, side.ws, side.ws_bytes, side.handle)
+        side_o, side_lse, side_ws, side_stream, main_stream = _ptr(side.o_acc), _ptr(side.lse), _ptr(side.ws), side.handle, main.cuda_stream
         for s in range(N):
             src, blk = plan(T, N, rank, s)
+            k, v = k_zz[src], v_zz[src]
             if s & 1:
-                B.mmsp_attn_step_fwd(shape, blk, q, k_zz[src], v_zz[src], side.o_acc, side.lse, True, side.ws,
-                                     side.ws_bytes, side.handle)
+                if s == 1:          # the side lane's first step stores; rows that it does not reach must hold an empty result
+                    end = blk.q_row0 + blk.n_q
+                    _fill_rows(shape, 0, blk.q_row0, q, k, v, side_o, side_lse, side_ws, side.ws_bytes, side_stream)
+                    _fill_rows(shape, end, n_rows - end, q, k, v, side_o, side_lse, side_ws, side.ws_bytes, side_stream)
+                B.mmsp_attn_step_fwd(shape, blk, q, k, v, side_o, side_lse, s > 1, side_ws, side.ws_bytes, side_stream)
             else:
-                B.mmsp_attn_step_fwd(shape, blk, q, k_zz[src], v_zz[src], o_acc, lse, s > 0, ws, ws_bytes,
-                                     main.cuda_stream)
+                B.mmsp_attn_step_fwd(shape, blk, q, k, v, o_acc, lse, s > 0, ws, ws_bytes, main_stream)
         main.wait_stream(side.stream)
-        B.mmsp_attn_merge(shape, 0, n_rows, o_acc, lse, side.o_acc, side.lse, o_final, stream=main.cuda_stream)
+        B.mmsp_attn_merge(shape, 0, n_rows, o_acc, lse, side_o, side_lse, o_final, stream=main_stream)
         return
     for s in range(N):
         src, blk = plan(T, N, rank, s)
@@ -98,17 +123,20 @@ def rank_backward(shape, T, N, rank, q, k_zz, v_zz, o_final, d_o, lse, delta, dq
     side.stream (with side's workspace).  `plan` as in rank_forward."""
     n_rows = q.shape[0]
     plan = plan or B.mmsp_zigzag_plan
+    k_zz, v_zz, dk_zz, dv_zz = (_block_ptrs(x, N) for x in (k_zz, v_zz, dk_zz, dv_zz))
+    q, o_final, d_o, lse, delta, dq, ws = (_ptr(x) for x in (q, o_final, d_o, lse, delta, dq, ws))
     if side is not None:
         import torch
         main = torch.cuda.current_stream()
-        B.mmsp_attn_delta(shape, 0, n_rows, o_final, d_o, delta, stream=main.cuda_stream)
+        main_stream, side_stream, side_ws = main.cuda_stream, side.handle, _ptr(side.ws)
+        B.mmsp_attn_delta(shape, 0, n_rows, o_final, d_o, delta, stream=main_stream)
         side.stream.wait_stream(main)
         for s in range(N):
             src, blk = plan(T, N, rank, s)
             B.mmsp_attn_step_bwd(shape, blk, q, k_zz[src], v_zz[src], None, d_o, lse, delta, False, dq, None, None,
-                                 False, ws, ws_bytes, main.cuda_stream)
+                                 False, ws, ws_bytes, main_stream)
             B.mmsp_attn_step_bwd(shape, blk, q, k_zz[src], v_zz[src], None, d_o, lse, delta, False, None,
-                                 dk_zz[src], dv_zz[src], False, side.ws, side.ws_bytes, side.handle)
+                                 dk_zz[src], dv_zz[src], False, side_ws, side.ws_bytes, side_stream)
         main.wait_stream(side.stream)
         return
     B.mmsp_attn_delta(shape, 0, n_rows, o_final, d_o, delta, stream=stream)
@@ -124,12 +152,17 @@ def rank_forward_packed(shape, T, N, rank, q, k_zz, v_zz, cu_seqlens, n_docs, o_
     on global positions): the sub-blocks of mmsp_zigzag_plan_packed, merged in the step epilogue.
     cu_host (host copy of cu_seqlens) lets the plan skip segment pairs that no document spans."""
     n_rows = q.shape[0]
-    B.mmsp_attn_step_fwd(shape, B.make_block(0, n_rows, 0, 0, B.MMSP_MASK_NONE, 0, 0), q, k_zz[0], v_zz[0], o_acc, lse,
-                         False, ws, ws_bytes, stream)          # rows whose document lies in no visited segment stay empty
+    k_zz, v_zz = _block_ptrs(k_zz, N), _block_ptrs(v_zz, N)
+    q, o_acc, lse, ws, cu_seqlens = _ptr(q), _ptr(o_acc), _ptr(lse), _ptr(ws), _ptr(cu_seqlens)
+    seen = set()                               # query segments that hold a result: the first sub-block of one stores
     for s in range(N):
         src, blks = B.mmsp_zigzag_plan_packed(T, N, rank, s, cu_seqlens, n_docs, cu_host)
         for blk in blks:
-            B.mmsp_attn_step_fwd(shape, blk, q, k_zz[src], v_zz[src], o_acc, lse, True, ws, ws_bytes, stream)
+            B.mmsp_attn_step_fwd(shape, blk, q, k_zz[src], v_zz[src], o_acc, lse, blk.q_row0 in seen, ws, ws_bytes, stream)
+            seen.add(blk.q_row0)
+    for row0 in (0, n_rows // 2):              # rows whose document lies in no visited segment
+        if row0 not in seen:
+            _fill_rows(shape, row0, n_rows // 2, q, k_zz[0], v_zz[0], o_acc, lse, ws, ws_bytes, stream)
     if o_final is not None:
         B.mmsp_attn_merge(shape, 0, n_rows, o_acc, lse, None, None, o_final, stream=stream)
 
@@ -139,6 +172,8 @@ def rank_backward_packed(shape, T, N, rank, q, k_zz, v_zz, cu_seqlens, n_docs, o
     """Backward of rank_forward_packed.  dq must be zero on entry; the key rows a step reaches
     are overwritten by its first sub-block and accumulated into by the next one."""
     n_rows = q.shape[0]
+    k_zz, v_zz, dk_zz, dv_zz = (_block_ptrs(x, N) for x in (k_zz, v_zz, dk_zz, dv_zz))
+    q, o_final, d_o, lse, delta, dq, ws, cu_seqlens = (_ptr(x) for x in (q, o_final, d_o, lse, delta, dq, ws, cu_seqlens))
     B.mmsp_attn_delta(shape, 0, n_rows, o_final, d_o, delta, stream=stream)
     for s in range(N):
         src, blks = B.mmsp_zigzag_plan_packed(T, N, rank, s, cu_seqlens, n_docs, cu_host)
