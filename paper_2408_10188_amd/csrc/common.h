@@ -34,19 +34,25 @@ struct StepArgs {
   int32_t rank;                 // bf16 kernels: whether workgroups may rank their tiles (may_rank)
 };
 
-// Heads per KV head, and what row_of_pair() needs to divide by it: floor(2^32 / group) + 1, 0 for a group of one.
+// Division of 0 <= i < 2^31 by a number the host knows.  The rounded-up reciprocal exceeds 1 / d by at most 2^-32, so the
+// product's upper half is the quotient or, at most, one more.  (A division of two runtime integers is some 35 dependent
+// instructions, of 64-bit ones over a hundred.)
+struct FastDiv {
+  uint32_t d, magic;                                    // magic: floor(2^32 / d) + 1, 0 for d = 1
+};
+inline FastDiv fast_div(int64_t d) { return {(uint32_t)d, d > 1 ? (uint32_t)((1ull << 32) / (uint64_t)d) + 1 : 0}; }
+__device__ __forceinline__ uint32_t operator/(uint32_t i, const FastDiv& f) {
+  if (f.magic == 0) return i;
+  const uint32_t q = __umulhi(i, f.magic);
+  return q - (q * f.d > i ? 1u : 0u);
+}
+
+// Heads per KV head; the row of pair i of a KV head's (row, head) list.
 inline void set_group(StepArgs& a, int group) {
   a.group = group;
-  a.group_magic = group > 1 ? (uint32_t)((1ull << 32) / (uint32_t)group) + 1 : 0;
+  a.group_magic = fast_div(group).magic;
 }
-// i / group for 0 <= i < 2^31.  The rounded-up reciprocal exceeds 1 / group by at most 2^-32, so the product's upper half
-// is the quotient or, at most, one more.  (A division of two runtime integers is some 35 dependent instructions, and a workgroup
-// needs several before its first copy.)
-__device__ __forceinline__ int row_of_pair(const StepArgs& a, int i) {
-  if (a.group_magic == 0) return i;
-  const uint32_t q = __umulhi((uint32_t)i, a.group_magic);
-  return (int)(q - (q * (uint32_t)a.group > (uint32_t)i ? 1u : 0u));
-}
+__device__ __forceinline__ int row_of_pair(const StepArgs& a, int i) { return (int)((uint32_t)i / FastDiv{(uint32_t)a.group, a.group_magic}); }
 
 // Workspace views of one backward call (all inside the caller's workspace).
 struct BwdWorkspace {
