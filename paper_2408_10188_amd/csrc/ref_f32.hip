@@ -362,29 +362,130 @@ __device__ __forceinline__ void dkdv_keys(const StepArgs& a, float* parts, int k
   }
 }
 
-// The first n_dkdv workgroups take key blocks (the longer chains), the others query blocks: both gradients need only what
-// the forward left, so one launch serves both where the chip has room for all of them at once.
-template <int D, bool kDkdv>
-__global__ __launch_bounds__(64 * kWaves) void bwd_f32_kernel(StepArgs a, int n_dkdv) {
-  __shared__ __attribute__((aligned(16))) float parts[(kDkdv ? 2 : 1) * kWaves * kPartFloats<D>];
-  const int b = blockIdx.x, kb = (a.n_k + kRows - 1) / kRows, qb = (a.n_q + kRows - 1) / kRows;
-  if (kDkdv && b < n_dkdv) dkdv_keys<D>(a, parts, b % kb, b / kb);
-  else dq_rows<D>(a, parts, (b - n_dkdv) % qb, (b - n_dkdv) / qb);
+// dK or dV alone (parts: kWaves * kPartFloats<D> floats): a shorter chain per element, and registers to spare, so that the
+// transposed rows are on their way before the first product needs anything.
+template <int D, bool kDv>
+__device__ __forceinline__ void grad_keys(const StepArgs& a, float* parts, int key_block, int kvh) {
+  constexpr bool kDk = !kDv;
+  constexpr int kNat = kDk ? D / 4 : 4;                 // V and dO in natural rows: for dK only
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, col = lane & 15;
+  const int key0 = key_block * kRows;
+  const int keyc = min(key0 + col, a.n_k - 1);
+  int lo, hi;
+  row_interval_of_key(a, CuGlobal{a.cu}, keyc, lo, hi);
+  const int lo_first = __builtin_amdgcn_readlane(lo, 0), hi_first = __builtin_amdgcn_readlane(hi, 0);
+  const int lo_last = __builtin_amdgcn_readlane(lo, 15), hi_last = __builtin_amdgcn_readlane(hi, 15);
+  const int qb0 = lo_first / kRows, n_qb = hi_last >= lo_first ? hi_last / kRows - qb0 + 1 : 0;
+  float k[D / 4], v[kNat];
+  {
+    const int64_t nat = (int64_t)(a.k_row0 + keyc) * a.kv_ts + (int64_t)kvh * a.kv_hs + g * (D / 4);
+    load_floats(k, reinterpret_cast<const float*>(a.k) + nat);
+    if constexpr (kDk) load_floats(v, reinterpret_cast<const float*>(a.v) + nat);
+  }
+  f32x4 acc[D / 16];
+#pragma unroll
+  for (int b = 0; b < D / 16; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float* qb_ = reinterpret_cast<const float*>(a.q) + (int64_t)a.q_row0 * a.q_ts;
+  const float* dob_ = reinterpret_cast<const float*>(a.d_o) + (int64_t)a.q_row0 * a.Hq * D;
+  for (int e = wave; e < n_qb * a.group; e += kWaves) {
+    const int h = kvh * a.group + e / n_qb, row0 = (qb0 + e % n_qb) * kRows;
+    const float* qh = qb_ + (int64_t)h * a.q_hs;
+    const float* doh = dob_ + (int64_t)h * D;
+    float zt[4][D / 16];
+    auto load_transposed = [&](const float* x, int64_t row_stride) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) load_floats(zt[i], x + (int64_t)min(row0 + g * 4 + i, a.n_q - 1) * row_stride + col * (D / 16));
+    };
+    float q[D / 4], d_o[kNat];
+    const int64_t rn = min(row0 + col, a.n_q - 1);
+    load_floats(q, qh + rn * a.q_ts + g * (D / 4));
+    if constexpr (kDk) load_floats(d_o, doh + rn * a.Hq * D + g * (D / 4));
+    float L[4], Dl[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t st = (int64_t)h * a.lse_hs + a.q_row0 + min(row0 + g * 4 + i, a.n_q - 1);
+      L[i] = a.lse_final[st];
+      if constexpr (kDk) Dl[i] = a.delta[st];
+    }
+    if constexpr (kDk) load_transposed(qh, a.q_ts);
+    else load_transposed(doh, (int64_t)a.Hq * D);
+    const f32x4 s = first_product<D>(q, k);
+    f32x4 dp = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (kDk) dp = first_product<D>(d_o, v);
+    bool hidden = row0 < lo_last || row0 + kRows - 1 > hi_first;
+    uint32_t seen = 0;
+    f32x4 p, ds;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = row0 + g * 4 + i;
+      const bool on = r >= lo && r <= hi && L[i] != -INFINITY;
+      p[i] = on ? expf(s[i] * a.scale - L[i]) : 0.f;
+      ds[i] = on ? p[i] * (dp[i] - Dl[i]) : 0.f;
+      seen |= (uint32_t)on << i;
+    }
+    hidden = hidden || __any(seen != 15u);
+    second_product<D>(acc, zt, kDv ? p : ds, hidden, seen, lane);
+  }
+  store_partial<D>(parts + wave * kPartFloats<D>, acc, lane);
+  __syncthreads();
+  for (int item = threadIdx.x; item < kRows * D / 4; item += 64 * kWaves) {
+    const int j = key0 + item / (D / 4);
+    if (j >= a.n_k) continue;
+    const float mul = kDv ? 1.f : a.scale;
+    float4 x = sum_partials<D>(parts, item);
+    x.x *= mul; x.y *= mul; x.z *= mul; x.w *= mul;
+    float4* p = reinterpret_cast<float4*>((kDv ? a.dv : a.dk) + ((int64_t)(a.k_row0 + j) * a.Hkv + kvh) * (int64_t)D) + item % (D / 4);
+    if (a.accumulate) {
+      const float4 y = *p;
+      x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
+    }
+    *p = x;
+  }
 }
 
+enum Roles { kRowsOnly, kRowsAndKeys, kRowsAndSplitKeys };
+
+// The first workgroups take key blocks (the longest chains; kRowsAndSplitKeys: n_keys for dK, then n_keys for dV), the others query blocks.
+template <int D, Roles kRoles>
+__global__ __launch_bounds__(64 * kWaves) void bwd_f32_kernel(StepArgs a, int n_keys) {
+  __shared__ __attribute__((aligned(16))) float parts[(kRoles == kRowsAndKeys ? 2 : 1) * kWaves * kPartFloats<D>];
+  int b = blockIdx.x;
+  const int kb = (a.n_k + kRows - 1) / kRows, qb = (a.n_q + kRows - 1) / kRows;
+  if constexpr (kRoles == kRowsAndKeys) {
+    if (b < n_keys) return dkdv_keys<D>(a, parts, b % kb, b / kb);
+    b -= n_keys;
+  }
+  if constexpr (kRoles == kRowsAndSplitKeys) {
+    if (b < n_keys) return grad_keys<D, false>(a, parts, b % kb, b / kb);
+    b -= n_keys;
+    if (b < n_keys) return grad_keys<D, true>(a, parts, b % kb, b / kb);
+    b -= n_keys;
+  }
+  dq_rows<D>(a, parts, b % qb, b / qb);
+}
+
+// All gradients need only what the forward left, so one launch serves them where the chip has room for all workgroups at once, and with room
+// to spare dK and dV are workgroups of their own: both need S, but what bounds them is the chain of loads and products of an
+// element, and that is shorter for one result.  Measured at d = 128, us as two launches / one launch / one with dK and dV
+// apart: 2/1 heads 256 x 256 causal 48.9 / 33.3 / 25.4, 4/1 800 x 800 (50 key blocks, 300 workgroups) 210 / 177 / 131;
+// 8/8 128 x 256 (128 key blocks, 320 workgroups) 31 / 20 / 25, 256 x 256 (384) 37 / 22 / 27, 800 x 800 (1200) 138 / - / 151.
 template <int D>
 hipError_t launch_bwd(const StepArgs& a, hipStream_t stream) {
   const int64_t n_dq = a.dq != nullptr ? (int64_t)((a.n_q + kRows - 1) / kRows) * a.Hq : 0;
-  const int64_t n_dkdv = a.dk != nullptr ? (int64_t)((a.n_k + kRows - 1) / kRows) * a.Hkv : 0;
+  const int64_t n_keys = a.dk != nullptr ? (int64_t)((a.n_k + kRows - 1) / kRows) * a.Hkv : 0;
+  const int64_t n_cu = cu_count();
   const dim3 b(64 * kWaves);
-  // A step of 256 rows and two heads: 20 us + 10 us as two launches, 20 us as one.  With more workgroups than CUs
-  // two launches, because a CU holds two of the smaller dQ workgroups.
-  if (n_dq > 0 && n_dkdv > 0 && n_dq + n_dkdv <= cu_count()) {
-    bwd_f32_kernel<D, true><<<dim3((unsigned)(n_dq + n_dkdv)), b, 0, stream>>>(a, (int)n_dkdv);
+  const int64_t apart = n_dq + 2 * n_keys;
+  if (n_keys > 0 && (apart <= n_cu || (apart <= n_cu * 5 / 4 && n_keys <= n_cu / 4))) {
+    bwd_f32_kernel<D, kRowsAndSplitKeys><<<dim3((unsigned)apart), b, 0, stream>>>(a, (int)n_keys);
     return hipGetLastError();
   }
-  if (n_dq > 0) bwd_f32_kernel<D, false><<<dim3((unsigned)n_dq), b, 0, stream>>>(a, 0);
-  if (n_dkdv > 0) bwd_f32_kernel<D, true><<<dim3((unsigned)n_dkdv), b, 0, stream>>>(a, (int)n_dkdv);
+  if (n_dq > 0 && n_keys > 0 && n_dq + n_keys <= n_cu) {
+    bwd_f32_kernel<D, kRowsAndKeys><<<dim3((unsigned)(n_dq + n_keys)), b, 0, stream>>>(a, (int)n_keys);
+    return hipGetLastError();
+  }
+  if (n_dq > 0) bwd_f32_kernel<D, kRowsOnly><<<dim3((unsigned)n_dq), b, 0, stream>>>(a, 0);
+  if (n_keys > 0) bwd_f32_kernel<D, kRowsAndKeys><<<dim3((unsigned)n_keys), b, 0, stream>>>(a, (int)n_keys);
   return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-"""Forward and backward steps at the edges of the forward's and the dQ kernel's tiles, against the fp64 oracle.  The rows of the heads that share
+"""Forward and backward steps at the edges of the kernels' tiles and of the rules that share them out, against the fp64 oracle.  The rows of the heads that share
 a KV head are one list cut into tiles of 128 or 256 (row, head) pairs, so an edge can fall between two heads of a row;
 the key loop takes four tiles of 64 per trip and starts in the middle of one."""
 import pytest
@@ -43,3 +43,14 @@ def test_shares_of_a_key_tile(hq, hkv, n_q, n_k, mask, pos):
 def test_a_causal_mask_that_hides_nothing(q_pos0):
     """From q_pos0 = 99 on no key of 0..99 follows the first query: such a block runs as one without a mask."""
     _run_step(True, 6, 2, 128, 64, 100, dict(q_row0=0, n_q=64, k_row0=0, n_k=100, mask=B.MMSP_MASK_CAUSAL_DIAG, q_pos0=q_pos0, k_pos0=0), seed=q_pos0)
+
+
+@pytest.mark.parametrize("hq,hkv,n_q,n_k", [
+    (2, 1, 37, 41), (8, 2, 399, 401),                        # dK and dV apart: 3 + 3 + 6 workgroups; 52 + 52 + 200, more than 256 in all
+    (8, 8, 120, 250),                                        # one launch, dK and dV together: 128 + 64
+    (8, 8, 257, 259),                                        # two launches: 136, 136
+])
+@pytest.mark.parametrize("d", [64, 128])
+def test_gradients_in_fp32_by_launches(hq, hkv, n_q, n_k, d):
+    for mask, pos, cu in ((B.MMSP_MASK_FULL, 0, None), (B.MMSP_MASK_CAUSAL_DIAG, n_k - n_q - 20, None), (B.MMSP_MASK_CAUSAL_DIAG, 0, [0, 3, 20, n_q])):
+        _run_step(False, hq, hkv, d, n_q + 2, n_k + 3, dict(q_row0=0, n_q=n_q, k_row0=0, n_k=n_k, mask=mask, q_pos0=pos, k_pos0=0), cu=cu, seed=n_q + d)
