@@ -86,6 +86,7 @@ def rank_forward(shape, T, N, rank, q, k_zz, v_zz, o_acc, lse, o_final=None, str
     mmsp_contiguous_plan, q and k_zz[r] hold the contiguous chunk r instead of the zigzag pair."""
     n_rows = q.shape[0]
     plan = plan or B.mmsp_zigzag_plan
+    _held = (q, k_zz, v_zz, o_acc, lse, ws)      # until the side stream has been waited for, whoever else still has them
     k_zz, v_zz = _block_ptrs(k_zz, N), _block_ptrs(v_zz, N)
     q, o_acc, lse, ws = _ptr(q), _ptr(o_acc), _ptr(lse), _ptr(ws)
     if side is not None and N > 1:
@@ -123,6 +124,7 @@ def rank_backward(shape, T, N, rank, q, k_zz, v_zz, o_final, d_o, lse, delta, dq
     side.stream (with side's workspace).  `plan` as in rank_forward."""
     n_rows = q.shape[0]
     plan = plan or B.mmsp_zigzag_plan
+    _held = (q, k_zz, v_zz, o_final, d_o, lse, delta, dq, dk_zz, dv_zz, ws)  # as in rank_forward
     k_zz, v_zz, dk_zz, dv_zz = (_block_ptrs(x, N) for x in (k_zz, v_zz, dk_zz, dv_zz))
     q, o_final, d_o, lse, delta, dq, ws = (_ptr(x) for x in (q, o_final, d_o, lse, delta, dq, ws))
     if side is not None:
@@ -152,6 +154,7 @@ def rank_forward_packed(shape, T, N, rank, q, k_zz, v_zz, cu_seqlens, n_docs, o_
     on global positions): the sub-blocks of mmsp_zigzag_plan_packed, merged in the step epilogue.
     cu_host (host copy of cu_seqlens) lets the plan skip segment pairs that no document spans."""
     n_rows = q.shape[0]
+    _held = (q, k_zz, v_zz, o_acc, lse, ws, cu_seqlens)  # until the last launch
     k_zz, v_zz = _block_ptrs(k_zz, N), _block_ptrs(v_zz, N)
     q, o_acc, lse, ws, cu_seqlens = _ptr(q), _ptr(o_acc), _ptr(lse), _ptr(ws), _ptr(cu_seqlens)
     seen = set()                               # query segments that hold a result: the first sub-block of one stores
@@ -172,6 +175,7 @@ def rank_backward_packed(shape, T, N, rank, q, k_zz, v_zz, cu_seqlens, n_docs, o
     """Backward of rank_forward_packed.  dq must be zero on entry; the key rows a step reaches
     are overwritten by its first sub-block and accumulated into by the next one."""
     n_rows = q.shape[0]
+    _held = (q, k_zz, v_zz, o_final, d_o, lse, delta, dq, dk_zz, dv_zz, ws, cu_seqlens)  # until the last launch
     k_zz, v_zz, dk_zz, dv_zz = (_block_ptrs(x, N) for x in (k_zz, v_zz, dk_zz, dv_zz))
     q, o_final, d_o, lse, delta, dq, ws, cu_seqlens = (_ptr(x) for x in (q, o_final, d_o, lse, delta, dq, ws, cu_seqlens))
     B.mmsp_attn_delta(shape, 0, n_rows, o_final, d_o, delta, stream=stream)
