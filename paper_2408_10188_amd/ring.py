@@ -157,15 +157,14 @@ def rank_forward_packed(shape, T, N, rank, q, k_zz, v_zz, cu_seqlens, n_docs, o_
     _held = (q, k_zz, v_zz, o_acc, lse, ws, cu_seqlens)  # until the last launch
     k_zz, v_zz = _block_ptrs(k_zz, N), _block_ptrs(v_zz, N)
     q, o_acc, lse, ws, cu_seqlens = _ptr(q), _ptr(o_acc), _ptr(lse), _ptr(ws), _ptr(cu_seqlens)
-    seen = set()                               # query segments that hold a result: the first sub-block of one stores
+    own = 2 * (T // (2 * N))
+    _fill_rows(shape, own, n_rows - own, q, k_zz[0], v_zz[0], o_acc, lse, ws, ws_bytes, stream)   # of a buffer that is longer
+    seen = set()                               # query segments that hold a result: the first sub-block of one stores, and step 0 reaches both
     for s in range(N):
         src, blks = B.mmsp_zigzag_plan_packed(T, N, rank, s, cu_seqlens, n_docs, cu_host)
         for blk in blks:
             B.mmsp_attn_step_fwd(shape, blk, q, k_zz[src], v_zz[src], o_acc, lse, blk.q_row0 in seen, ws, ws_bytes, stream)
             seen.add(blk.q_row0)
-    for row0 in (0, n_rows // 2):              # rows whose document lies in no visited segment
-        if row0 not in seen:
-            _fill_rows(shape, row0, n_rows // 2, q, k_zz[0], v_zz[0], o_acc, lse, ws, ws_bytes, stream)
     if o_final is not None:
         B.mmsp_attn_merge(shape, 0, n_rows, o_acc, lse, None, None, o_final, stream=stream)
 
