@@ -59,21 +59,34 @@ def _ptr(t):
     return t.data_ptr() if hasattr(t, "data_ptr") else t
 
 
-def _block_ptrs(x, n):
-    """Addresses of x[0] .. x[n-1].  Indexing a tensor makes a new one each time, which took longer than the call it was
-    made for: a step of a small ring waited for the host."""
+class _Made:
+    """Addresses of the blocks of a sequence that is not one tensor, asked for when a step needs them.  Indexing may make the block,
+    so it is kept: the newest until the next is asked for (its launch is in the queue by then, and the stream's order protects its
+    memory from there on), every one of them where a side stream reads them too."""
+
+    def __init__(self, blocks, keep_all):
+        self.blocks, self.keep_all, self.kept = blocks, keep_all, []
+
+    def __getitem__(self, r):
+        if not self.keep_all:
+            self.kept.clear()
+        self.kept.append(self.blocks[r])
+        return _ptr(self.kept[-1])
+
+
+def _blocks(x, n, side=None):
+    """x[r] of 0 <= r < n as an address.  A tensor's are computed once: indexing it makes a new one each time, which took longer than
+    the call it was made for, and a step of a small ring waited for the host."""
     if not hasattr(x, "data_ptr"):
-        return [_ptr(x[r]) for r in range(n)]
-    if x.shape[0] < n:
-        raise IndexError("%d blocks given, %d needed" % (x.shape[0], n))
+        return _Made(x, side is not None)
     base, step = x.data_ptr(), x.stride(0) * x.element_size()
-    return [base + r * step for r in range(n)]
+    return [base + r * step for r in range(min(n, x.shape[0]))]
 
 
-def _fill_rows(shape, row0, n_rows, q, k, v, o, lse, ws, ws_bytes, stream):
+def _fill_rows(shape, row0, n_rows, q, o, lse, ws, ws_bytes, stream):
     """An empty result for rows that no step reaches."""
     if n_rows > 0:
-        B.mmsp_attn_step_fwd(shape, B.make_block(row0, n_rows, 0, 0, B.MMSP_MASK_NONE, 0, 0), q, k, v, o, lse, False, ws, ws_bytes, stream)
+        B.mmsp_attn_step_fwd(shape, B.make_block(row0, n_rows, 0, 0, B.MMSP_MASK_NONE, 0, 0), q, q, q, o, lse, False, ws, ws_bytes, stream)
 
 
 def rank_forward(shape, T, N, rank, q, k_zz, v_zz, o_acc, lse, o_final=None, stream=0, fused_merge=True,
@@ -87,7 +100,7 @@ def rank_forward(shape, T, N, rank, q, k_zz, v_zz, o_acc, lse, o_final=None, str
     n_rows = q.shape[0]
     plan = plan or B.mmsp_zigzag_plan
     _held = (q, k_zz, v_zz, o_acc, lse, ws)      # until the side stream has been waited for, whoever else still has them
-    k_zz, v_zz = _block_ptrs(k_zz, N), _block_ptrs(v_zz, N)
+    k_zz, v_zz = _blocks(k_zz, N, side), _blocks(v_zz, N, side)
     q, o_acc, lse, ws = _ptr(q), _ptr(o_acc), _ptr(lse), _ptr(ws)
     if side is not None and N > 1:
         main = _fork(side)
@@ -98,8 +111,8 @@ def rank_forward(shape, T, N, rank, q, k_zz, v_zz, o_acc, lse, o_final=None, str
             if s & 1:
                 if s == 1:          # the side lane's first step stores; rows that it does not reach must hold an empty result
                     end = blk.q_row0 + blk.n_q
-                    _fill_rows(shape, 0, blk.q_row0, q, k, v, side_o, side_lse, side_ws, side.ws_bytes, side_stream)
-                    _fill_rows(shape, end, n_rows - end, q, k, v, side_o, side_lse, side_ws, side.ws_bytes, side_stream)
+                    _fill_rows(shape, 0, blk.q_row0, q, side_o, side_lse, side_ws, side.ws_bytes, side_stream)
+                    _fill_rows(shape, end, n_rows - end, q, side_o, side_lse, side_ws, side.ws_bytes, side_stream)
                 B.mmsp_attn_step_fwd(shape, blk, q, k, v, side_o, side_lse, s > 1, side_ws, side.ws_bytes, side_stream)
             else:
                 B.mmsp_attn_step_fwd(shape, blk, q, k, v, o_acc, lse, s > 0, ws, ws_bytes, main_stream)
@@ -125,7 +138,7 @@ def rank_backward(shape, T, N, rank, q, k_zz, v_zz, o_final, d_o, lse, delta, dq
     n_rows = q.shape[0]
     plan = plan or B.mmsp_zigzag_plan
     _held = (q, k_zz, v_zz, o_final, d_o, lse, delta, dq, dk_zz, dv_zz, ws)  # as in rank_forward
-    k_zz, v_zz, dk_zz, dv_zz = (_block_ptrs(x, N) for x in (k_zz, v_zz, dk_zz, dv_zz))
+    k_zz, v_zz, dk_zz, dv_zz = (_blocks(x, N, side) for x in (k_zz, v_zz, dk_zz, dv_zz))
     q, o_final, d_o, lse, delta, dq, ws = (_ptr(x) for x in (q, o_final, d_o, lse, delta, dq, ws))
     if side is not None:
         import torch
@@ -155,10 +168,10 @@ def rank_forward_packed(shape, T, N, rank, q, k_zz, v_zz, cu_seqlens, n_docs, o_
     cu_host (host copy of cu_seqlens) lets the plan skip segment pairs that no document spans."""
     n_rows = q.shape[0]
     _held = (q, k_zz, v_zz, o_acc, lse, ws, cu_seqlens)  # until the last launch
-    k_zz, v_zz = _block_ptrs(k_zz, N), _block_ptrs(v_zz, N)
+    k_zz, v_zz = _blocks(k_zz, N), _blocks(v_zz, N)
     q, o_acc, lse, ws, cu_seqlens = _ptr(q), _ptr(o_acc), _ptr(lse), _ptr(ws), _ptr(cu_seqlens)
     own = 2 * (T // (2 * N))
-    _fill_rows(shape, own, n_rows - own, q, k_zz[0], v_zz[0], o_acc, lse, ws, ws_bytes, stream)   # of a buffer that is longer
+    _fill_rows(shape, own, n_rows - own, q, o_acc, lse, ws, ws_bytes, stream)   # of a buffer that is longer
     seen = set()                               # query segments that hold a result: the first sub-block of one stores, and step 0 reaches both
     for s in range(N):
         src, blks = B.mmsp_zigzag_plan_packed(T, N, rank, s, cu_seqlens, n_docs, cu_host)
@@ -175,7 +188,7 @@ def rank_backward_packed(shape, T, N, rank, q, k_zz, v_zz, cu_seqlens, n_docs, o
     are overwritten by its first sub-block and accumulated into by the next one."""
     n_rows = q.shape[0]
     _held = (q, k_zz, v_zz, o_final, d_o, lse, delta, dq, dk_zz, dv_zz, ws, cu_seqlens)  # until the last launch
-    k_zz, v_zz, dk_zz, dv_zz = (_block_ptrs(x, N) for x in (k_zz, v_zz, dk_zz, dv_zz))
+    k_zz, v_zz, dk_zz, dv_zz = (_blocks(x, N) for x in (k_zz, v_zz, dk_zz, dv_zz))
     q, o_final, d_o, lse, delta, dq, ws, cu_seqlens = (_ptr(x) for x in (q, o_final, d_o, lse, delta, dq, ws, cu_seqlens))
     B.mmsp_attn_delta(shape, 0, n_rows, o_final, d_o, delta, stream=stream)
     for s in range(N):
