@@ -449,7 +449,7 @@ enum Roles { kRowsOnly, kRowsAndKeys, kRowsAndSplitKeys };
 template <int D, Roles kRoles>
 __global__ __launch_bounds__(64 * kWaves) void bwd_f32_kernel(StepArgs a, int n_keys) {
   __shared__ __attribute__((aligned(16))) float parts[(kRoles == kRowsAndKeys ? 2 : 1) * kWaves * kPartFloats<D>];
-  int b = blockIdx.x;
+  int b = blockIdx.y * gridDim.x + blockIdx.x;           // roles apart: (blocks, heads), which one dimension need not hold (2^32 threads)
   const int kb = (a.n_k + kRows - 1) / kRows, qb = (a.n_q + kRows - 1) / kRows;
   if constexpr (kRoles == kRowsAndKeys) {
     if (b < n_keys) return dkdv_keys<D>(a, parts, b % kb, b / kb);
@@ -471,8 +471,9 @@ __global__ __launch_bounds__(64 * kWaves) void bwd_f32_kernel(StepArgs a, int n_
 // 8/8 128 x 256 (128 key blocks, 320 workgroups) 31 / 20 / 25, 256 x 256 (384) 37 / 22 / 27, 800 x 800 (1200) 138 / - / 151.
 template <int D>
 hipError_t launch_bwd(const StepArgs& a, hipStream_t stream) {
-  const int64_t n_dq = a.dq != nullptr ? (int64_t)((a.n_q + kRows - 1) / kRows) * a.Hq : 0;
-  const int64_t n_keys = a.dk != nullptr ? (int64_t)((a.n_k + kRows - 1) / kRows) * a.Hkv : 0;
+  const dim3 row_blocks((a.n_q + kRows - 1) / kRows, a.Hq), key_blocks((a.n_k + kRows - 1) / kRows, a.Hkv);
+  const int64_t n_dq = a.dq != nullptr ? (int64_t)row_blocks.x * a.Hq : 0;
+  const int64_t n_keys = a.dk != nullptr ? (int64_t)key_blocks.x * a.Hkv : 0;
   const int64_t n_cu = cu_count();
   const dim3 b(64 * kWaves);
   const int64_t apart = n_dq + 2 * n_keys;
@@ -484,8 +485,8 @@ hipError_t launch_bwd(const StepArgs& a, hipStream_t stream) {
     bwd_f32_kernel<D, kRowsAndKeys><<<dim3((unsigned)(n_dq + n_keys)), b, 0, stream>>>(a, (int)n_keys);
     return hipGetLastError();
   }
-  if (n_dq > 0) bwd_f32_kernel<D, kRowsOnly><<<dim3((unsigned)n_dq), b, 0, stream>>>(a, 0);
-  if (n_keys > 0) bwd_f32_kernel<D, kRowsAndKeys><<<dim3((unsigned)n_keys), b, 0, stream>>>(a, (int)n_keys);
+  if (n_dq > 0) bwd_f32_kernel<D, kRowsOnly><<<row_blocks, b, 0, stream>>>(a, 0);
+  if (n_keys > 0) bwd_f32_kernel<D, kRowsAndKeys><<<key_blocks, b, 0, stream>>>(a, (int)n_keys);
   return hipGetLastError();
 }
 
