@@ -121,7 +121,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_i
   const char* const k_first = reinterpret_cast<const char*>(a.k) + kv_off;
   const char* const v_first = reinterpret_cast<const char*>(a.v) + kv_off;
   TileCopier<kCopies> copier;
-  copier.init(a.kv_ts, a.n_k, kt1, wave, lane);
+  copier.init(lds, a.kv_ts, a.n_k, kt1, wave, lane);
   auto fetch = [&](int t, int slot) {
     const auto k = copier.tile(k_first, t), v = copier.tile(v_first, t);
 #pragma unroll

@@ -125,7 +125,7 @@ __global__ __launch_bounds__(512, 2) void fwd_bf16_kernel(StepArgs a, int n_item
   const char* const k_first = reinterpret_cast<const char*>(a.k) + kv_off;
   const char* const v_first = reinterpret_cast<const char*>(a.v) + kv_off;
   TileCopier<kCopies> copier;
-  copier.init(a.kv_ts, a.n_k, kt1, wave, lane);
+  copier.init(lds, a.kv_ts, a.n_k, kt1, wave, lane);
   auto fetch = [&](const char* first, int t, int slot_offset) {
     const auto x = copier.tile(first, t);
 #pragma unroll

@@ -189,14 +189,14 @@ struct TileCopier {
   static constexpr int W = 16 / kCopies;               // wavefronts that share a tile
   uint32_t tile_bytes;
   int last, ragged;                                    // last tile to fetch, the one that is not whole (or -1)
-  int lds_wave;                                        // start of the wavefront's first copy inside a slot
+  int lds_wave;                                        // LDS address of the wavefront's first copy in the array's first slot
   uint32_t off, copy_bytes, ragged_limit;              // of the wavefront's first copy; from one to its next
-  __device__ __forceinline__ void init(int64_t row_stride_elems, int rows, int last_tile, int wave, int lane) {
+  __device__ __forceinline__ void init(const void* lds_array, int64_t row_stride_elems, int rows, int last_tile, int wave, int lane) {
     const uint32_t row_bytes = (uint32_t)row_stride_elems * 2, chunk = ((lane & 15) ^ ((lane >> 4) << 2)) << 4;
     tile_bytes = 64 * row_bytes;
     last = last_tile;
     ragged = rows % 64 != 0 ? rows / 64 : -1;
-    lds_wave = __builtin_amdgcn_readfirstlane(wave) * kGroupPitch;
+    lds_wave = (int)lds_address(lds_array) + __builtin_amdgcn_readfirstlane(wave) * kGroupPitch;
     ragged_limit = (ragged >= 0 ? rows % 64 - 1 : 63) * row_bytes + chunk;
     off = (4 * wave + (lane >> 4)) * row_bytes + chunk;
     copy_bytes = 4 * W * row_bytes;
@@ -207,7 +207,7 @@ struct TileCopier {
     t = min(t, last);
     return {first + (uint64_t)(uint32_t)t * tile_bytes, t == ragged ? ragged_limit : 0xffffffffu};
   }
-  // the wavefront's copy i of a tile into the slot at byte kSlot of the kernel's LDS array (which starts at LDS address 0)
+  // the wavefront's copy i of a tile into the slot at byte `slot_offset` of the LDS array
   __device__ __forceinline__ void copy(const Tile& x, int i, int slot_offset) const {
     const uint32_t o = min(off + i * copy_bytes, x.limit);
     asm volatile("s_add_i32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_wave), "v"(o), "s"(x.base), "i"(slot_offset + i * W * kGroupPitch) : "memory", "scc");
