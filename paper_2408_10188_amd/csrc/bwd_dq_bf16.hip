@@ -335,8 +335,6 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_i
     iteration(std::integral_constant<int, 2>(), t + 2);
     iteration(std::integral_constant<int, 3>(), t + 3);
   }
-  __builtin_amdgcn_s_waitcnt(0x0F70);                   // the copies issued past the end have landed, everybody is done with the tiles:
-  lds_barrier();                                        // the result can pass through LDS
   // lane, half and column anew: kept from above they would take registers that the loop is short of
   const int lane_e = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), half_e = lane_e >> 5, col_e = lane_e & 31;
   float* const out = kPartial ? part + (int64_t)split * a.n_q * a.Hq * 128 : a.dq + (int64_t)a.q_row0 * a.Hq * 128;
@@ -345,11 +343,13 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_i
   };
   const int row_up = tile_row0 + wave_s * 32 + half_e;   // this half of the wavefront takes every other row from here on
   float4 old[16];
-  if (!kPartial) {                                       // all sixteen on their way before anything waits
+  if (!kPartial) {                                       // on their way before the drain of the copies (28/4 heads, 64 x 64: 10.0 us behind it, 8.9 here)
 #pragma unroll
     for (int i = 0; i < 16; ++i)
       if (row_up + 2 * i < n_rows) old[i] = *result_at(row_up + 2 * i);
   }
+  __builtin_amdgcn_s_waitcnt(0x0F70);                   // the copies issued past the end have landed, everybody is done with the tiles:
+  lds_barrier();                                        // the result can pass through LDS
   char* const area = lds + wave_s * kResultBytes;
   result_to_lds(area, dq, a.scale, half_e, col_e);
 #pragma unroll
