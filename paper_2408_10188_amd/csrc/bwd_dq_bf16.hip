@@ -25,15 +25,15 @@ namespace {
 
 constexpr int kBN = 64;            // keys per tile
 
-// n_items: work items per KV head, row tiles of kWaves * 32 rows of its list (x nsplit ranges of their keys).
+// n_items: work items per KV head, tiles of tile_rows <= kWaves * 32 rows of its list (x nsplit ranges of their keys).
 // kPartial: nsplit workgroups share the key tiles of every row tile, each stores its share of dQ in
 // part [nsplit][n_q][Hq][128] for launch_dq_combine.
 // The launch bound of 512 holds for four wavefronts too: with fewer the compiler would use the accumulation registers
 // that a lone wavefront per SIMD has, and copy every S and dP out of them.
 template <int kWaves, bool kPartial>
-__global__ __launch_bounds__(512, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_items, int xcd_bits, int nsplit, float* part,
+__global__ __launch_bounds__(512, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_items, int tile_rows, int xcd_bits, int nsplit, float* part,
                                                              BwdWorkspace stats) {
-  constexpr int kBM = 32 * kWaves;                      // rows per workgroup
+  constexpr int kBM = 32 * kWaves;                      // most rows of a workgroup
   constexpr int kCopies = 16 / kWaves;
   constexpr int kDepth = 4;                              // LDS operand reads in flight
   // LDS map: the four K slots, then the four V slots; slots are selected at compile time (the loop is unrolled four tiles
@@ -72,18 +72,19 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_i
     tile = __builtin_amdgcn_readfirstlane(block * a.group + sub);
   }
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-  const int n_rows = a.n_q * a.group, tile_row0 = tile * kBM;
+  const int n_rows = a.n_q * a.group, tile_row0 = tile * tile_rows;
   if (tile_row0 >= n_rows) return;
+  const int row_end = min(tile_row0 + tile_rows, n_rows);
   const int row = tile_row0 + wave * 32 + col;          // this lane's row of the list
-  const bool live = row < n_rows;
-  const int rowc = min(row, n_rows - 1);
+  const bool live = row < row_end;
+  const int rowc = min(row, row_end - 1);
   const int q_row = row_of_pair(a, rowc), h = kvh * a.group + rowc - q_row * a.group;
 
   int lo, hi;
   key_interval_of_row(a, cu, q_row, lo, hi);
   int t_lo, t_hi, dummy;
   key_interval_of_row(a, cu, row_of_pair(a, tile_row0), t_lo, dummy);
-  key_interval_of_row(a, cu, row_of_pair(a, min(tile_row0 + kBM, n_rows) - 1), dummy, t_hi);
+  key_interval_of_row(a, cu, row_of_pair(a, row_end - 1), dummy, t_hi);
   // wavefront: smallest and largest lo and hi, those of its first and last row
   const int w_lo_min = __builtin_amdgcn_readlane(lo, 0), w_hi_min = __builtin_amdgcn_readlane(hi, 0);
   const int w_lo_max = __builtin_amdgcn_readlane(lo, 31), w_hi_max = __builtin_amdgcn_readlane(hi, 31);
@@ -103,7 +104,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_i
   kvh = __builtin_amdgcn_readfirstlane(kvh);
   // Tiles that one of this wavefront's rows sees.  Outside them it only helps to move tiles, which leaves the SIMD
   // to the wavefront it shares it with (documents shorter than a tile's rows, rows past the end of the list).
-  const bool w_any = w_lo_min <= w_hi_max && tile_row0 + wave * 32 < n_rows;
+  const bool w_any = w_lo_min <= w_hi_max && tile_row0 + wave * 32 < row_end;
   const int t_last = w_hi_max / kBN;
   int t_first = w_any ? max(w_lo_min / kBN, kt0) : 1 << 30;
   const uint32_t t_span = w_any && t_last > t_first ? t_last - t_first : 0;
@@ -161,7 +162,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_i
       stats.nl2[(int64_t)h * padded + q_row] = neg_l2;
       stats.ndl[(int64_t)h * padded + q_row] = -Dl;
     }
-    if (tile_row0 + kBM >= n_rows) {                    // the padding of every head of the group: the last tile's workgroup
+    if (row_end == n_rows) {                            // the padding of every head of the group: the last tile's workgroup
       for (int i = tid; i < (padded - a.n_q) * a.group; i += 64 * kWaves) {
         const int pad = row_of_pair(a, i);
         const int64_t at = (int64_t)(kvh * a.group + i - pad * a.group) * padded + a.n_q + pad;
@@ -346,7 +347,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_i
   if (!kPartial) {                                       // on their way before the drain of the copies (28/4 heads, 64 x 64: 10.0 us behind it, 8.9 here)
 #pragma unroll
     for (int i = 0; i < 16; ++i)
-      if (row_up + 2 * i < n_rows) old[i] = *result_at(row_up + 2 * i);
+      if (row_up + 2 * i < row_end) old[i] = *result_at(row_up + 2 * i);
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);                   // the copies issued past the end have landed, everybody is done with the tiles:
   lds_barrier();                                        // the result can pass through LDS
@@ -356,16 +357,17 @@ __global__ __launch_bounds__(512, 2) void bwd_dq_bf16_kernel(StepArgs a, int n_i
   for (int i = 0; i < 16; ++i) {
     float4 o = result_chunk(area, 2 * i + half_e, col_e);
     if (!kPartial) { o.x += old[i].x; o.y += old[i].y; o.z += old[i].z; o.w += old[i].w; }
-    if (row_up + 2 * i < n_rows) *result_at(row_up + 2 * i) = o;
+    if (row_up + 2 * i < row_end) *result_at(row_up + 2 * i) = o;
   }
 }
 
 template <int kWaves>
-hipError_t launch(StepArgs a, const BwdWorkspace& st, int nsplit, float* part, hipStream_t stream) {
+hipError_t launch(StepArgs a, const BwdWorkspace& st, const KeyRanges& r, float* part, hipStream_t stream) {
   constexpr int kBM = 32 * kWaves;
-  const int n_blocks_q = (a.n_q + kBM - 1) / kBM;
+  const int n_blocks_q = (a.n_q + kBM - 1) / kBM, nsplit = r.count;
   a.rank = may_rank(a, n_blocks_q, n_blocks_q * nsplit * a.Hq, 1, 5);
-  const int n_items = (a.rank ? n_blocks_q * a.group : (int)(((int64_t)a.n_q * a.group + kBM - 1) / kBM)) * nsplit;
+  const int rows = a.rank ? kBM : r.rows;
+  const int n_items = (a.rank ? n_blocks_q * a.group : (int)(((int64_t)a.n_q * a.group + rows - 1) / rows)) * nsplit;
   int xcd_bits = -1, n_blocks = n_items * a.Hkv;
   if (8 % a.Hkv == 0) {
     xcd_bits = __builtin_ctz(8 / a.Hkv);
@@ -373,11 +375,11 @@ hipError_t launch(StepArgs a, const BwdWorkspace& st, int nsplit, float* part, h
   }
   const dim3 g(n_blocks), b(64 * kWaves);
   if (nsplit > 1) {
-    bwd_dq_bf16_kernel<kWaves, true><<<g, b, 0, stream>>>(a, n_items, xcd_bits, nsplit, part, st);
+    bwd_dq_bf16_kernel<kWaves, true><<<g, b, 0, stream>>>(a, n_items, rows, xcd_bits, nsplit, part, st);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : launch_dq_combine(a, part, nsplit, stream);
   }
-  bwd_dq_bf16_kernel<kWaves, false><<<g, b, 0, stream>>>(a, n_items, xcd_bits, 1, nullptr, st);
+  bwd_dq_bf16_kernel<kWaves, false><<<g, b, 0, stream>>>(a, n_items, rows, xcd_bits, 1, nullptr, st);
   return hipGetLastError();
 }
 
@@ -390,7 +392,7 @@ hipError_t launch_bwd_dq_bf16(const StepArgs& a, const BwdWorkspace* stats_out, 
   // Two documents' keys for any number of query tiles (the forward: one to two): a tile costs more here, so a cut pays sooner.
   const KeyRanges r = pick_key_ranges(a, 1.6, (int64_t)a.n_q * a.Hq * 128 * sizeof(float), a.ws_bytes - stats, 2.);
   float* part = reinterpret_cast<float*>(a.ws + stats);
-  return r.waves == 4 ? launch<4>(a, st, r.count, part, stream) : launch<8>(a, st, r.count, part, stream);
+  return r.waves == 4 ? launch<4>(a, st, r, part, stream) : launch<8>(a, st, r, part, stream);
 }
 
 }  // namespace mmsp

@@ -199,7 +199,7 @@ hipError_t launch_bwd_stats(const float* lse, const float* delta, int64_t lse_hs
 int cu_count();
 double mean_document(const StepArgs& a);
 int32_t may_rank(const StepArgs& a, int n_tiles, int n_blocks, int heads_per_tile, int max_rounds);
-struct KeyRanges { int waves, count; };                 // wavefronts of a workgroup, workgroups that share a tile's keys
+struct KeyRanges { int waves, count, rows; };           // wavefronts of a workgroup, workgroups that share a tile's keys, rows of a tile
 KeyRanges pick_key_ranges(const StepArgs& a, double tile_us, int64_t bytes_per_range, int64_t room, double mean_documents);
 hipError_t launch_fwd_combine(const StepArgs& a, const float* part_o, const float* part_lse, int nsplit, hipStream_t stream);
 hipError_t launch_dq_combine(const StepArgs& a, const float* part, int nsplit, hipStream_t stream);

@@ -32,13 +32,13 @@ constexpr int kBN = 64;            // keys per tile
 
 enum Result { kStore, kMerge, kPartial };
 
-// n_items: work items per KV head, row tiles of kWaves * 32 rows of its list (x nsplit ranges of their keys).
+// n_items: work items per KV head, tiles of tile_rows <= kWaves * 32 rows of its list (x nsplit ranges of their keys).
 // kPartial: nsplit workgroups share the key tiles of every query tile, each stores its (O, LSE) in
 // part_o [nsplit][n_q][Hq][128] and part_lse [nsplit][Hq][n_q] for launch_fwd_combine.
 template <int kWaves, Result kResult>
-__global__ __launch_bounds__(512, 2) void fwd_bf16_kernel(StepArgs a, int n_items, int xcd_bits, int nsplit, float* part_o,
+__global__ __launch_bounds__(512, 2) void fwd_bf16_kernel(StepArgs a, int n_items, int tile_rows, int xcd_bits, int nsplit, float* part_o,
                                                                            float* part_lse) {
-  constexpr int kBM = 32 * kWaves;                      // rows per workgroup
+  constexpr int kBM = 32 * kWaves;                      // most rows of a workgroup
   constexpr int kCopies = 16 / kWaves;
   constexpr int kDepth = 4;                              // LDS operand reads in flight
   // Tile t lives in slot (t - first) % 4 of its ring; slots are selected at compile time (the loop is unrolled four
@@ -79,11 +79,12 @@ __global__ __launch_bounds__(512, 2) void fwd_bf16_kernel(StepArgs a, int n_item
       block = heaviest_first(n_blocks - 1 - block, n_blocks, 64 * kWaves, reinterpret_cast<int*>(lds), [&](int i) { return key_tiles_of_rows(a, cu, i * kBM, kBM); });
     tile = block * a.group + sub;
   }
-  const int n_rows = a.n_q * a.group, tile_row0 = tile * kBM;
+  const int n_rows = a.n_q * a.group, tile_row0 = tile * tile_rows;
   if (tile_row0 >= n_rows) return;
+  const int row_end = min(tile_row0 + tile_rows, n_rows);
   const int row = tile_row0 + wave * 32 + col;          // this lane's row of the list
-  const bool live = row < n_rows;
-  const int rowc = min(row, n_rows - 1);
+  const bool live = row < row_end;
+  const int rowc = min(row, row_end - 1);
   const int q_row = row_of_pair(a, rowc), h = kvh * a.group + rowc - q_row * a.group;
 
   // visible key interval of this lane's row, and of the workgroup / wavefront extremes
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(512, 2) void fwd_bf16_kernel(StepArgs a, int n_item
   key_interval_of_row(a, cu, q_row, lo, hi);
   int t_lo, t_hi, dummy;
   key_interval_of_row(a, cu, row_of_pair(a, tile_row0), t_lo, dummy);
-  key_interval_of_row(a, cu, row_of_pair(a, min(tile_row0 + kBM, n_rows) - 1), dummy, t_hi);
+  key_interval_of_row(a, cu, row_of_pair(a, row_end - 1), dummy, t_hi);
   // wavefront: smallest and largest lo and hi, those of its first and last row
   const int w_lo_min = __builtin_amdgcn_readlane(lo, 0), w_hi_min = __builtin_amdgcn_readlane(hi, 0);
   const int w_lo_max = __builtin_amdgcn_readlane(lo, 31), w_hi_max = __builtin_amdgcn_readlane(hi, 31);
@@ -110,7 +111,7 @@ __global__ __launch_bounds__(512, 2) void fwd_bf16_kernel(StepArgs a, int n_item
   // Iterations this wavefront has work in: from the one that computes S of its first tile to the one
   // that multiplies P of its last.  Outside them it only helps to move tiles, which leaves the SIMD
   // to the wavefront it shares it with (documents shorter than a tile's rows, rows past the end of the list).
-  const bool w_any = w_lo_min <= w_hi_max && tile_row0 + wave_s * 32 < n_rows;
+  const bool w_any = w_lo_min <= w_hi_max && tile_row0 + wave_s * 32 < row_end;
   int t_first = w_any ? max(w_lo_min / kBN - 1, kt0) : 1 << 30, t_last = w_any ? w_hi_max / kBN + 1 : -1;
   // In vector registers on purpose: branches on them are then mask changes that the register allocator takes in its
   // stride, where the same branches as jumps make it spill the accumulators.
@@ -379,7 +380,7 @@ __global__ __launch_bounds__(512, 2) void fwd_bf16_kernel(StepArgs a, int n_item
     if (live) la = *lp;
 #pragma unroll
     for (int i = 0; i < 16; ++i)
-      if (row_up + 2 * i < n_rows) old[i] = *result_at(row_up + 2 * i);
+      if (row_up + 2 * i < row_end) old[i] = *result_at(row_up + 2 * i);
   }
   __builtin_amdgcn_sched_barrier(0);
 
@@ -424,7 +425,7 @@ __global__ __launch_bounds__(512, 2) void fwd_bf16_kernel(StepArgs a, int n_item
   for (int i = 0; i < 16; ++i) {
     const int rr = 2 * i + half;
     float4 o = result_chunk(area, rr, col);
-    bool on = row_up + 2 * i < n_rows;
+    bool on = row_up + 2 * i < row_end;
     if (kResult == kMerge) {
       const float w = weights[rr];
       on = on && w != kSkip;
@@ -439,11 +440,12 @@ __global__ __launch_bounds__(512, 2) void fwd_bf16_kernel(StepArgs a, int n_item
 namespace {
 
 template <int kWaves>
-hipError_t launch(StepArgs a, int nsplit, hipStream_t stream) {
+hipError_t launch(StepArgs a, const KeyRanges& r, hipStream_t stream) {
   constexpr int kBM = 32 * kWaves;
-  const int n_blocks_q = (a.n_q + kBM - 1) / kBM;
+  const int n_blocks_q = (a.n_q + kBM - 1) / kBM, nsplit = r.count;
   a.rank = may_rank(a, n_blocks_q, n_blocks_q * nsplit * a.Hq, 1, 5);
-  const int n_items = (a.rank ? n_blocks_q * a.group : (int)(((int64_t)a.n_q * a.group + kBM - 1) / kBM)) * nsplit;
+  const int rows = a.rank ? kBM : r.rows;
+  const int n_items = (a.rank ? n_blocks_q * a.group : (int)(((int64_t)a.n_q * a.group + rows - 1) / rows)) * nsplit;
   int xcd_bits = -1, n_blocks = n_items * a.Hkv;
   if (8 % a.Hkv == 0) {
     xcd_bits = __builtin_ctz(8 / a.Hkv);
@@ -453,12 +455,12 @@ hipError_t launch(StepArgs a, int nsplit, hipStream_t stream) {
   if (nsplit > 1) {
     float* part_o = reinterpret_cast<float*>(a.ws);
     float* part_lse = part_o + (int64_t)nsplit * a.n_q * a.Hq * 128;
-    fwd_bf16_kernel<kWaves, kPartial><<<g, b, 0, stream>>>(a, n_items, xcd_bits, nsplit, part_o, part_lse);
+    fwd_bf16_kernel<kWaves, kPartial><<<g, b, 0, stream>>>(a, n_items, rows, xcd_bits, nsplit, part_o, part_lse);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : launch_fwd_combine(a, part_o, part_lse, nsplit, stream);
   }
-  if (a.accumulate) fwd_bf16_kernel<kWaves, kMerge><<<g, b, 0, stream>>>(a, n_items, xcd_bits, 1, nullptr, nullptr);
-  else fwd_bf16_kernel<kWaves, kStore><<<g, b, 0, stream>>>(a, n_items, xcd_bits, 1, nullptr, nullptr);
+  if (a.accumulate) fwd_bf16_kernel<kWaves, kMerge><<<g, b, 0, stream>>>(a, n_items, rows, xcd_bits, 1, nullptr, nullptr);
+  else fwd_bf16_kernel<kWaves, kStore><<<g, b, 0, stream>>>(a, n_items, rows, xcd_bits, 1, nullptr, nullptr);
   return hipGetLastError();
 }
 
@@ -469,7 +471,7 @@ hipError_t launch_fwd_bf16(const StepArgs& a, hipStream_t stream) {
   // The slowest query tile counts: one tile lies anywhere in a document, of eight one lies late in a long one.
   const double mean_documents = 1. + (n_blocks_q < 8 ? n_blocks_q - 1 : 7) / 7.;
   const KeyRanges r = pick_key_ranges(a, 1.2, (int64_t)a.n_q * a.Hq * 129 * sizeof(float), a.ws_bytes, mean_documents);
-  return r.waves == 4 ? launch<4>(a, r.count, stream) : launch<8>(a, r.count, stream);
+  return r.waves == 4 ? launch<4>(a, r, stream) : launch<8>(a, r, stream);
 }
 
 }  // namespace mmsp

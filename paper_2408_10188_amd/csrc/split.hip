@@ -153,6 +153,10 @@ int32_t may_rank(const StepArgs& a, int n_tiles, int n_blocks, int heads_per_til
 // costs 5 to 10 us; half of all keys, whatever n_docs, was such a cut for every block of short documents (100 rows on
 // 8192 keys, 28/4 heads, documents of 60..300: forward 16 us uncut, 25 us cut, 14.6 us by this rule, which does not cut).
 // At most bwd_dkdv_partial_bytes() are used, so that a workspace larger than asked for changes no result.
+// Blocks so small that uncut tiles of 128 leave half of the CUs idle are cut into tiles of 64 or 32 rows, whose spare wavefronts help
+// to move tiles: what a launch of one or two key tiles takes is the reading and writing of the rows of one workgroup.  28/4 heads,
+// 64 x 64 causal, tiles of 128 / 32 rows: forward 7.5 / 7.0 us, merging 9.4 / 8.7, dQ 8.9 / 7.9; 4/2 heads, 500 x 500: 14.1 / 13.3,
+// 15.8 / 15.1, 16.3 / 15.0.
 KeyRanges pick_key_ranges(const StepArgs& a, double tile_us, int64_t bytes_per_range, int64_t room, double mean_documents) {
   room = std::min(room, bwd_dkdv_partial_bytes());
   const double tile[2] = {tile_us, .73 * tile_us};
@@ -161,7 +165,7 @@ KeyRanges pick_key_ranges(const StepArgs& a, double tile_us, int64_t bytes_per_r
   const int n_cu = cu_count();
   const int64_t rows = (int64_t)a.n_q * a.group;        // of one KV head
   const int64_t blocks[2] = {(rows + 255) / 256 * a.Hkv, (rows + 127) / 128 * a.Hkv};
-  KeyRanges best = {8, 1};
+  KeyRanges best = {8, 1, 256};
   if (blocks[0] >= n_cu || bytes_per_range <= 0) return best;
   int64_t keys = a.n_k;
   if (a.mask == 1) keys = std::max<int64_t>(0, std::min<int64_t>(keys, (int64_t)a.q_pos0 + a.n_q - a.k_pos0));
@@ -173,8 +177,10 @@ KeyRanges pick_key_ranges(const StepArgs& a, double tile_us, int64_t bytes_per_r
     for (int n = 1; n <= most; ++n) {
       const int64_t rounds = (blocks[w] * n + n_cu - 1) / n_cu;
       const double cost = rounds * (tiles / n * tile[w] + kStart[w]) + (n > 1 ? kLaunch + 2. * n * (double)bytes_per_range / kBytesPerUs : 0.);
-      if (cost < best_cost) { best = {w ? 4 : 8, n}; best_cost = cost; }
+      if (cost < best_cost) { best = {w ? 4 : 8, n, w ? 128 : 256}; best_cost = cost; }
     }
+  if (best.waves == 4 && best.count == 1)
+    while (best.rows > 32 && (rows + best.rows / 2 - 1) / (best.rows / 2) * a.Hkv <= n_cu) best.rows /= 2;
   return best;
 }
 
