@@ -21,6 +21,7 @@
 // of block b+1.  The operand of every matrix instruction is read from LDS four instructions ahead.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "mfma_tiles.h"
 
@@ -480,11 +481,18 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restric
   const float* src = partial + (int64_t)blockIdx.y * nsplit * slot_elems + i * 4;
   float4* dst = reinterpret_cast<float4*>(blockIdx.y ? dv : dk) + i;
   float4 x = accumulate ? *dst : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 8
-  for (int sidx = 0; sidx < nsplit; ++sidx) {
-    const float4 p = *reinterpret_cast<const float4*>(src + sidx * slot_elems);
-    x.x += p.x; x.y += p.y; x.z += p.z; x.w += p.w;
-  }
+  auto add_up = [&](auto all, int s0) {                 // the partial results from s0 on, at most eight
+    float4 p[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (all || s0 + j < nsplit) p[j] = *reinterpret_cast<const float4*>(src + (s0 + j) * slot_elems);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (all || s0 + j < nsplit) { x.x += p[j].x; x.y += p[j].y; x.z += p[j].z; x.w += p[j].w; }
+  };
+  int s0 = 0;
+  for (; s0 + 8 <= nsplit; s0 += 8) add_up(std::true_type(), s0);
+  if (s0 < nsplit) add_up(std::false_type(), s0);        // all on their way at once too: 28/4 heads, 50 x 50, seven shares 16.2 -> 15.0 us
   *dst = x;
 }
 
