@@ -98,8 +98,8 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
     item = slot * xcd_per_kv + (xcd % xcd_per_kv);
     if (item >= n_kt * nsplit) return;
   } else {
-    kvh = blockIdx.x / (n_kt * nsplit);
-    item = blockIdx.x % (n_kt * nsplit);
+    item = blockIdx.x / a.Hkv;      // heavy tiles of every KV head first
+    kvh = blockIdx.x - item * a.Hkv;
   }
   int kt = item / nsplit;
   const int split = item % nsplit;
@@ -504,30 +504,78 @@ constexpr int kSplitMaxRanges = 32;
 
 int64_t bwd_dkdv_partial_bytes() { return 2LL * kSplitMaxBlocks * kKeys * 128 * (int64_t)sizeof(float); }
 
-// Into how many shares a key tile's (query tile, head) sequence is dealt: what minimises an estimate in us.  A share costs
-// kStart plus t per element (64 rows of one head; less under a mask, where CUs that are done early leave their power to the
-// others); with every pair visible all workgroups carry the same work and come in whole rounds, under a mask the heaviest
-// counts, or the sum over all CUs where that is more (heavy tiles come first).  The reduction costs a launch and one
-// write and one read of every partial result (3.3 TB/s measured).  Measured, us with 1 / 2 / 3 / 4 / 5 / 6 / 8 / 12 shares:
-//   28/4 heads, 760 x 1520:          156  93  71  62  56  77  69 156 (5 are 240 workgroups; 12 do not fit)
-//   8/8 heads, 320 x 640:             18  22  24  25  27  29  36  38
-//   7/1 heads, 2560 x 2560 causal:   350 189 134 105  88  78  66  54
-//   4/2 heads, 50 rows behind 8000:   16  31  35  44 (before this estimate: as many as fill the chip, at most 8)
+// What the key tiles of a launch have to do, in elements (64 rows of one head), heaviest first: `full` tiles of `most`, then tiles
+// falling evenly to `least`; the rest sees nothing.
+struct TileWork { int tiles, full, seen; double most, least; };
+
+// Estimated us of the launch with n shares per tile.  A workgroup takes kElement for each of its elements and as much as kStart (kEmpty: without
+// any) of them to begin and to store its result; the launch lasts as long as its longest chain of workgroups, or as the sum over all CUs.  Workgroups go
+// to XCDs and shader engines in turn and wait for a CU of theirs, so that workgroup n_cu + k follows one a thirty-second
+// further up, not the one that ends first (7/1 heads, 1500 rows behind 10000, three shares: 270 workgroups, the last 14 of them short,
+// 154 us; in order of the ends they would take 126).  The reduction costs a launch, and every partial result is written and read.
+static double dkdv_us(const TileWork& w, int n_kv_heads, int n) {
+  constexpr double kElement = 1.2, kStart = 7., kEmpty = 2., kFixed = 8., kLaunch = 2.2, kMegabyte = .34;
+  const int n_cu = cu_count(), step = n_cu / 8, per_tile = n_kv_heads * n, blocks = w.tiles * per_tile;
+  auto workgroup = [&](int i) {
+    if (i >= blocks) return 0.;
+    const int t = i / per_tile;
+    const double e = t < w.full ? w.most : t < w.seen ? w.most + (w.least - w.most) * (t - w.full + 1) / (w.seen - w.full) : 0.;
+    return e > 0. ? std::ceil(e / n - 1e-9) + kStart : kEmpty;
+  };
+  const double elements = n_kv_heads * (w.full * w.most + (w.seen - w.full) * (w.most + w.least) / 2);
+  double longest = std::max(workgroup(0), (elements + per_tile * (w.seen * kStart + (w.tiles - w.seen) * kEmpty)) / n_cu);
+  if (blocks > n_cu) {
+    const int last = (std::min(blocks, 2 * n_cu) - 1 - n_cu) / step;
+    for (int x : {0, last / 2, last}) longest = std::max(longest, workgroup(std::max(0, n_cu - step - step * x)) + workgroup(n_cu + step * x));
+  }
+  const double megabytes = 2e-6 * kKeys * 128 * sizeof(float) * blocks;
+  return kFixed + kElement * longest + (n > 1 ? kLaunch + kMegabyte * megabytes : 0.);
+}
+
+// Into how many shares a key tile's (query tile, head) sequence is dealt.  Without documents, or with one, the host knows what every key
+// tile sees; of several it knows only how many there are, and one long document wants another count than many of the mean length.
+// So the count that gives every CU one workgroup (two where tiles differ), at most eight, is left only for one that the estimate finds
+// faster, by 3 %, or with several documents by 10 % both if one of them holds everything and if the longest is twice the mean.
+// Measured with every count up to 32: 1276 blocks without documents (8 arrangements of heads, 50 to 4000 rows on 50 to 34000 keys, with
+// and without a causal mask) take 1.0 % longer than with their best count in the mean, 247 blocks of packs as synth.py draws
+// them 2.5 %; 375 with made-up documents (clips, halves, one long first or last, few rows behind many keys) 3.5 %, where the
+// count that fills the CUs takes 20 % and a rule that trusts the mean length up to three times as long.  us by count:
+//   28/4 heads, 760 x 1520:               1: 152  2: 91  3: 68  4: 51  5: 47  6: 73 (288 workgroups)
+//   8/8 heads, 320 x 640:                 1: 17  2: 21  4: 25  6: 28
+//   28/4 heads, 1000 rows behind 3000:    1: 158  2: 111  3: 142  4: 123 (nearly all tiles see all rows: whole rounds)
+//   7/1 heads, 2500 x 2500 causal:        1: 361  4: 104  8: 65  16: 49  24: 54
+//   4/2 heads, 4000 x 4000, documents:    one long 1: 221  2: 124  4: 80  8: 76;  clips of 60 to 300 1: 30  2: 30  4: 38  8: 48
 static int pick_shares(const StepArgs& a, int n_kt) {
-  const double n_cu = cu_count(), base = (double)n_kt * a.Hkv, slot_bytes = 2. * kKeys * 128 * sizeof(float) * base;
+  const int base = n_kt * a.Hkv, q_tiles = (int)tiles_of(a.n_q);
+  const int limit = (int)std::min<int64_t>({kSplitMaxRanges, kSplitMaxBlocks / base, (int64_t)q_tiles * a.group});
+  if (limit <= 1) return 1;
   const bool even = a.mask == 0 && a.cu == nullptr;
-  double most = (double)tiles_of(a.n_q) * a.group;      // elements of the heaviest key tile
-  if (a.cu != nullptr) most = std::min(most, (2. * mean_document(a) / kBQ + 1.) * a.group);
-  const double t = even ? 1.75 : 1.4, mean = even ? most : .5 * most;
-  constexpr double kStart = 6., kLaunch = 4., kBytesPerUs = 3.3e6;
-  const int limit = (int)std::min({(double)kSplitMaxRanges, (double)bwd_dkdv_partial_bytes() / slot_bytes, most});
-  int best = 1;
-  double best_cost = 1e300;
-  for (int n = 1; n == 1 || n <= limit; ++n) {
-    const double share = std::ceil(most / n) * t + kStart, blocks = base * n;
-    const double kernel = even ? std::ceil(blocks / n_cu) * share : std::max(share, 1.1 * (base * mean * t + blocks * kStart) / n_cu);
-    const double cost = kernel + (n > 1 ? kLaunch + n * slot_bytes / kBytesPerUs : 0.);
-    if (cost < best_cost) { best = n; best_cost = cost; }
+  TileWork w[2];
+  int n_w = 1;
+  w[0] = {n_kt, n_kt, n_kt, (double)q_tiles * a.group, (double)q_tiles * a.group};
+  const int64_t behind = (int64_t)a.q_pos0 - a.k_pos0;   // keys that lie before the first row
+  if (a.mask == 1) {
+    w[0].seen = (int)std::max<int64_t>(0, std::min<int64_t>(n_kt, (behind + a.n_q + kKeys - 1) / kKeys));
+    w[0].full = std::min<int64_t>(w[0].seen, behind >= 0 ? behind / kKeys + 1 : 0);
+    const int64_t hidden = std::min<int64_t>(a.n_q - 1, std::max<int64_t>(0, (int64_t)(w[0].seen - 1) * kKeys - behind));
+    w[0].least = (double)(q_tiles - hidden / kBQ) * a.group;
+  }
+  const bool guess = a.cu != nullptr && a.n_docs > 1;
+  if (guess) {
+    const double mean = mean_document(a);
+    const int before = (int)std::max(0., std::min((behind - mean) / kKeys, (double)n_kt));   // tiles of earlier documents
+    n_w = 2;
+    w[1] = {n_kt, 0, std::max(1, w[0].seen - before), std::min<double>(q_tiles, 2. * mean / kBQ + 2.) * a.group, std::min(q_tiles, 2) * (double)a.group};
+  }
+  const int fill = std::max(1, std::min({(even ? cu_count() : 2 * cu_count()) / base, 8, limit}));
+  double with_fill[2];
+  for (int k = 0; k < n_w; ++k) with_fill[k] = dkdv_us(w[k], a.Hkv, fill);
+  int best = fill;
+  double best_ratio = guess ? .9 : .97;
+  for (int n = 1; n <= limit; ++n) {
+    double ratio = 0.;
+    for (int k = 0; k < n_w; ++k) ratio = std::max(ratio, dkdv_us(w[k], a.Hkv, n) / with_fill[k]);
+    if (ratio < best_ratio) { best = n; best_ratio = ratio; }
   }
   return best;
 }

@@ -30,7 +30,7 @@ def test_documents_shorter_than_a_tile(hq, hkv, cu):
 
 
 @pytest.mark.parametrize("hq,hkv,n_q,n_k,mask,pos", [
-    (7, 1, 1300, 130, B.MMSP_MASK_FULL, 0),                  # 147 elements a key tile, dealt to some twenty workgroups
+    (7, 1, 1300, 130, B.MMSP_MASK_FULL, 0),                  # 147 elements a key tile, dealt to 32 workgroups
     (7, 1, 1100, 1100, B.MMSP_MASK_CAUSAL_DIAG, 0),
     (5, 5, 70, 900, B.MMSP_MASK_CAUSAL_DIAG, 830),           # two elements: not dealt out
     (4, 2, 200, 129, B.MMSP_MASK_CAUSAL_DIAG, -20),          # one live key in the last tile, rows that see nothing
