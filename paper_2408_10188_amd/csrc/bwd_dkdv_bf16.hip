@@ -20,7 +20,6 @@
 // turn dP of block b into dS; while it accumulates dV and dK of block b they take the exponentials
 // of block b+1.  The operand of every matrix instruction is read from LDS four instructions ahead.
 #include <algorithm>
-#include <cmath>
 #include <type_traits>
 
 #include "mfma_tiles.h"
@@ -513,14 +512,15 @@ struct TileWork { int tiles, full, seen; double most, least; };
 // to XCDs and shader engines in turn and wait for a CU of theirs, so that workgroup n_cu + k follows one a thirty-second
 // further up, not the one that ends first (7/1 heads, 1500 rows behind 10000, three shares: 270 workgroups, the last 14 of them short,
 // 154 us; in order of the ends they would take 126).  The reduction costs a launch, and every partial result is written and read.
-static double dkdv_us(const TileWork& w, int n_kv_heads, int n) {
+static double dkdv_us(const TileWork& w, int n_kv_heads, int n, int n_cu) {
   constexpr double kElement = 1.2, kStart = 7., kEmpty = 2., kFixed = 8., kLaunch = 2.2, kMegabyte = .34;
-  const int n_cu = cu_count(), step = n_cu / 8, per_tile = n_kv_heads * n, blocks = w.tiles * per_tile;
+  const int step = n_cu / 8, per_tile = n_kv_heads * n, blocks = w.tiles * per_tile;
+  const double fall = (w.least - w.most) / std::max(1, w.seen - w.full), per_n = 1. / n;
   auto workgroup = [&](int i) {
     if (i >= blocks) return 0.;
     const int t = i / per_tile;
-    const double e = t < w.full ? w.most : t < w.seen ? w.most + (w.least - w.most) * (t - w.full + 1) / (w.seen - w.full) : 0.;
-    return e > 0. ? std::ceil(e / n - 1e-9) + kStart : kEmpty;
+    if (t >= w.seen) return kEmpty;
+    return (int)((w.most + fall * std::max(0, t - w.full + 1)) * per_n + (1. - 1e-9)) + kStart;   // rounded up
   };
   const double elements = n_kv_heads * (w.full * w.most + (w.seen - w.full) * (w.most + w.least) / 2);
   double longest = std::max(workgroup(0), (elements + per_tile * (w.seen * kStart + (w.tiles - w.seen) * kEmpty)) / n_cu);
@@ -546,7 +546,7 @@ static double dkdv_us(const TileWork& w, int n_kv_heads, int n) {
 //   7/1 heads, 2500 x 2500 causal:        1: 361  4: 104  8: 65  16: 49  24: 54
 //   4/2 heads, 4000 x 4000, documents:    one long 1: 221  2: 124  4: 80  8: 76;  clips of 60 to 300 1: 30  2: 30  4: 38  8: 48
 static int pick_shares(const StepArgs& a, int n_kt) {
-  const int base = n_kt * a.Hkv, q_tiles = (int)tiles_of(a.n_q);
+  const int base = n_kt * a.Hkv, q_tiles = (int)tiles_of(a.n_q), n_cu = cu_count();
   const int limit = (int)std::min<int64_t>({kSplitMaxRanges, kSplitMaxBlocks / base, (int64_t)q_tiles * a.group});
   if (limit <= 1) return 1;
   const bool even = a.mask == 0 && a.cu == nullptr;
@@ -567,14 +567,14 @@ static int pick_shares(const StepArgs& a, int n_kt) {
     n_w = 2;
     w[1] = {n_kt, 0, std::max(1, w[0].seen - before), std::min<double>(q_tiles, 2. * mean / kBQ + 2.) * a.group, std::min(q_tiles, 2) * (double)a.group};
   }
-  const int fill = std::max(1, std::min({(even ? cu_count() : 2 * cu_count()) / base, 8, limit}));
+  const int fill = std::max(1, std::min({(even ? n_cu : 2 * n_cu) / base, 8, limit}));
   double with_fill[2];
-  for (int k = 0; k < n_w; ++k) with_fill[k] = dkdv_us(w[k], a.Hkv, fill);
+  for (int k = 0; k < n_w; ++k) with_fill[k] = dkdv_us(w[k], a.Hkv, fill, n_cu);
   int best = fill;
   double best_ratio = guess ? .9 : .97;
   for (int n = 1; n <= limit; ++n) {
     double ratio = 0.;
-    for (int k = 0; k < n_w; ++k) ratio = std::max(ratio, dkdv_us(w[k], a.Hkv, n) / with_fill[k]);
+    for (int k = 0; k < n_w && ratio < best_ratio; ++k) ratio = std::max(ratio, dkdv_us(w[k], a.Hkv, n, n_cu) / with_fill[k]);
     if (ratio < best_ratio) { best = n; best_ratio = ratio; }
   }
   return best;
