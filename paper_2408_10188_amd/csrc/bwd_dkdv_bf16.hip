@@ -63,7 +63,8 @@ __device__ __forceinline__ void mfma32_v(f32x16& d, const u32x4& a, const u32x4&
 // nsplit > 1: the (query tile, head) sequence of every key tile is dealt out to nsplit
 // workgroups, which store their partial dK / dV into w.partial for dkdv_reduce_kernel to sum
 // (used when one workgroup per key tile would leave CUs idle or unevenly loaded).
-template <bool kMask>
+// kAdd: add to dk and dv (nsplit is 1; the reduction does it otherwise).
+template <bool kMask, bool kAdd>
 __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs a, BwdWorkspace w, int n_kt, int xcd_per_kv,
                                                                        int nsplit) {
   // LDS map: four Q tile slots in [0, 64 KiB), four dO tile slots in [64 KiB, 128 KiB), then the four
@@ -105,6 +106,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
   const CuLocal cu = local_cu(a, reinterpret_cast<int32_t*>(lds + 8192), 64 * kWaves);
   if (kMask && worth_ranking(a, cu, a.k_pos0, a.k_pos0 + a.n_k - 1))
     kt = heaviest_first(kt, n_kt, 64 * kWaves, reinterpret_cast<int*>(lds), [&](int i) { return query_tiles_of_keys(a, cu, i * kKeys, kKeys); });
+  kt = __builtin_amdgcn_readfirstlane(kt);
   const int tile_key0 = kt * kKeys;
   const int key = tile_key0 + wave * 32 + col;           // block-relative key of this lane
   const int keyc = min(key, a.n_k - 1);                  // a lane past the end repeats the last key: a column of its own that nobody stores
@@ -133,7 +135,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
     const int total = ntiles * a.group;
     niter = total > split ? (total - split + nsplit - 1) / nsplit : 0;
   }
-  if (niter == 0 && nsplit == 1 && a.accumulate) return;   // nothing visible, nothing to add
+  if (kAdd && niter == 0) return;                          // nothing visible, nothing to add
 
   const float c = a.scale * kLog2e;
 
@@ -142,6 +144,35 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
   for (int db = 0; db < 4; ++db)
 #pragma unroll
     for (int i = 0; i < 16; ++i) { dv[db][i] = 0.f; dk[db][i] = 0.f; }
+
+  // The results pass through LDS: into the partial result of this range, summed by dkdv_reduce_kernel, or where they belong.
+  // Each store takes two whole rows; workgroups take the rows in different orders.  They end at the same time and their tiles lie at
+  // distances of a power of two, so that in one order all of them write to a few memory channels at a time (4/2 heads,
+  // 1000 x 2000, eight shares, 256 workgroups: 36.3 us in one order, 32.5 in several).  The i-th store takes rows turn ^ 2 i, in LDS at
+  // addresses that an exclusive or turns into each other.
+  const int turn = (2 * (7 * kt + 5 * split + 3 * kvh) & 31) + half, keys_up = a.n_k - (tile_key0 + wave_s * 32);
+  int64_t rows[2];                                       // the wavefront's first row of dK and of dV, bytes from the pointer below
+#pragma unroll
+  for (int which = 0; which < 2; ++which) {
+    const int64_t first = nsplit > 1 ? ((int64_t)(which ? nsplit : 0) + split) * n_kt * kKeys : a.k_row0;
+    rows[which] = ((first + tile_key0 + wave_s * 32) * a.Hkv + kvh) * 512;
+    asm volatile("" : "+s"(rows[which]));                // or it is computed anew for every store
+  }
+  auto result_at = [&](int which, int i) {               // where this lane's 16 bytes of the i-th store go
+    char* const out = reinterpret_cast<char*>(nsplit > 1 ? w.partial : which ? a.dv : a.dk) + rows[which];
+    return reinterpret_cast<float4*>(out + ((uint32_t)(turn ^ 2 * i) * (uint32_t)(a.Hkv * 512) + col * 16));
+  };
+  auto each_store = [&](auto f) {
+    if (keys_up >= 32) {
+#pragma unroll
+      for (int n = 0; n < 32; ++n) f(n >> 4, n & 15);
+    } else {
+#pragma unroll
+      for (int n = 0; n < 32; ++n)
+        if ((turn ^ 2 * (n & 15)) < keys_up) f(n >> 4, n & 15);
+    }
+  };
+  float4 old[2][16];
 
   if (niter > 0) {
     // ---- asynchronous tile fetch: cursor over the (head of the group, query tile) sequence ----
@@ -433,39 +464,22 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
       if (it + 1 < niter) body(false, qs1, os1, st1, qs2, os2, st2, qs0, os0, st0);
       if (it + 2 < niter) body(false, qs2, os2, st2, qs3, os3, st3, qs1, os1, st1);
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);                  // drain the copies issued past the end before the workgroup leaves
+    // What is added to is read here, all of it at once, beside the drain of the copies: a launch of few tiles has nothing later to hide
+    // the latency (4/2 heads, 32 x 32: 18.2 us with dK's and then dV's read behind the barrier, 13.7 here).
+    if (kAdd) each_store([&](int which, int i) { old[which][i] = *result_at(which, i); });
+    __builtin_amdgcn_s_waitcnt(0x0F70);                  // the copies issued past the end have landed
   }
 
-  // The results pass through LDS (everybody is done with the tiles, and the copies issued past the end have landed): into the
-  // partial result of this range, summed by dkdv_reduce_kernel, or where they belong.
-  lds_barrier();
+  lds_barrier();                                         // everybody is done with the tiles: the results can pass through LDS
   char* const area = lds + wave * 2 * kResultBytes;
+  const int chunk = turn * 512 + ((col ^ turn) << 4);
   result_to_lds(area, dk, a.scale, half, col);
   result_to_lds(area + kResultBytes, dv, 1.f, half, col);
-  const bool partial = nsplit > 1, add = a.accumulate && !partial;
-  const int64_t slot_elems = (int64_t)n_kt * kKeys * a.Hkv * 128, rows_at = ((int64_t)(partial ? 0 : a.k_row0) * a.Hkv + kvh) * 128;
-  // Each store takes two whole rows; workgroups take the rows in different orders.  They end at the same time and their tiles lie at
-  // distances of a power of two, so that in one order all of them write to a few memory channels at a time (4/2 heads,
-  // 1000 x 2000, eight shares, 256 workgroups: 36.3 us in one order, 32.5 in several).
-  const int turn = 2 * (7 * kt + 5 * split + 3 * kvh) + half, key_up = tile_key0 + wave * 32;
-#pragma unroll
-  for (int which = 0; which < 2; ++which) {
-    float* const out = (partial ? w.partial + ((int64_t)(which ? nsplit : 0) + split) * slot_elems : which ? a.dv : a.dk) + rows_at;
-    auto result_at = [&](int key) { return reinterpret_cast<float4*>(out + (int64_t)key * a.Hkv * 128) + col; };
-    float4 old[16];
-    if (add) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (key_up + ((turn + 2 * i) & 31) < a.n_k) old[i] = *result_at(key_up + ((turn + 2 * i) & 31));
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int r = (turn + 2 * i) & 31;
-      float4 o = result_chunk(area + which * kResultBytes, r, col);
-      if (add) { o.x += old[i].x; o.y += old[i].y; o.z += old[i].z; o.w += old[i].w; }
-      if (key_up + r < a.n_k) *result_at(key_up + r) = o;
-    }
-  }
+  each_store([&](int which, int i) {
+    float4 o = *reinterpret_cast<const float4*>(area + which * kResultBytes + (chunk ^ i * (2 * 512 + 2 * 16)));   // result_chunk of that row
+    if (kAdd) { o.x += old[which][i].x; o.y += old[which][i].y; o.z += old[which][i].z; o.w += old[which][i].w; }
+    *result_at(which, i) = o;
+  });
 }
 #undef MMSP_PIN
 #undef MMSP_PIN_ACC
@@ -592,8 +606,10 @@ hipError_t launch_bwd_dkdv_bf16(const StepArgs& args, const BwdWorkspace& w, hip
     xcd_per_kv = 8 / a.Hkv;
     n_blocks = 8 * ((n_items + xcd_per_kv - 1) / xcd_per_kv);
   }
-  if (no_mask) bwd_dkdv_bf16_kernel<false><<<dim3(n_blocks), dim3(64 * kWaves), 0, stream>>>(a, w, n_kt, xcd_per_kv, nsplit);
-  else bwd_dkdv_bf16_kernel<true><<<dim3(n_blocks), dim3(64 * kWaves), 0, stream>>>(a, w, n_kt, xcd_per_kv, nsplit);
+  const bool add = a.accumulate && nsplit == 1;
+  const auto kernel = no_mask ? (add ? bwd_dkdv_bf16_kernel<false, true> : bwd_dkdv_bf16_kernel<false, false>)
+                              : (add ? bwd_dkdv_bf16_kernel<true, true> : bwd_dkdv_bf16_kernel<true, false>);
+  kernel<<<dim3(n_blocks), dim3(64 * kWaves), 0, stream>>>(a, w, n_kt, xcd_per_kv, nsplit);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || nsplit == 1) return e;
   const int64_t n4 = (int64_t)a.n_k * a.Hkv * 32;
