@@ -167,10 +167,10 @@ int32_t may_rank(const StepArgs& a, int n_tiles, int n_blocks, int heads_per_til
 // costs 5 to 10 us; half of all keys, whatever n_docs, was such a cut for every block of short documents (100 rows on
 // 8192 keys, 28/4 heads, documents of 60..300: forward 16 us uncut, 25 us cut, 14.6 us by this rule, which does not cut).
 // At most bwd_dkdv_partial_bytes() are used, so that a workspace larger than asked for changes no result.
-// Blocks so small that uncut tiles of 128 leave half of the CUs idle are cut into tiles of 64 or 32 rows, whose spare wavefronts help
+// Blocks so small that uncut tiles of 128 leave half of the CUs idle are cut into tiles of 64 to 8 rows, whose spare wavefronts help
 // to move tiles: what a launch of one or two key tiles takes is the reading and writing of the rows of one workgroup.  28/4 heads,
-// 64 x 64 causal, tiles of 128 / 32 rows: forward 7.5 / 7.0 us, merging 9.4 / 8.7, dQ 8.9 / 7.9; 4/2 heads, 500 x 500: 14.1 / 13.3,
-// 15.8 / 15.1, 16.3 / 15.0.
+// 48 x 48 causal, tiles of 128 / 32 / 8 rows: forward 8.3 / 7.8 / 7.4 us, merging 10.1 / 9.6 / 8.6, dQ 9.5 / 8.5 / 7.3 (fewer than 8 gain nothing
+// more); 4/2 heads, 128 x 128: 9.3 / 8.7 / 8.2, 11.0 / 10.4 / 9.5, 10.7 / 9.6 / 8.3.
 KeyRanges pick_key_ranges(const StepArgs& a, double tile_us, int64_t bytes_per_range, int64_t room, double mean_documents) {
   room = std::min(room, bwd_dkdv_partial_bytes());
   const double tile[2] = {tile_us, .73 * tile_us};
@@ -194,7 +194,7 @@ KeyRanges pick_key_ranges(const StepArgs& a, double tile_us, int64_t bytes_per_r
       if (cost < best_cost) { best = {w ? 4 : 8, n, w ? 128 : 256}; best_cost = cost; }
     }
   if (best.waves == 4 && best.count == 1)
-    while (best.rows > 32 && (rows + best.rows / 2 - 1) / (best.rows / 2) * a.Hkv <= n_cu) best.rows /= 2;
+    while (best.rows > 8 && (rows + best.rows / 2 - 1) / (best.rows / 2) * a.Hkv <= n_cu) best.rows /= 2;
   return best;
 }
 

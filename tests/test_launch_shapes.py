@@ -87,8 +87,8 @@ def test_a_grid_dimension_holds_fewer_than_2_32_threads(library, what, hq, hkv, 
 
 @pytest.mark.parametrize("what", ["fwd", "dq"])
 def test_rows_of_a_small_block_are_spread_over_the_chip(library, what):
-    """Tiles of 32 (row, head) pairs where they fit the CUs, then of 64 and 128; four wavefronts in each."""
-    for hq, hkv, n_q, n_k, tiles in [(28, 4, 50, 50, 11), (28, 4, 300, 64, 66 // 2), (28, 4, 600, 64, 33), (8, 8, 500, 64, 16), (4, 2, 1, 64, 1)]:
+    """Tiles of 8 (row, head) pairs where they fit the CUs, then of 16 to 128; four wavefronts in each."""
+    for hq, hkv, n_q, n_k, tiles in [(28, 4, 50, 50, 44), (28, 4, 300, 64, 33), (28, 4, 600, 64, 33), (8, 8, 500, 64, 32), (4, 2, 1, 64, 1)]:
         (x, y, z, threads), = launches(library, what, hq, hkv, n_q, n_k, 0)
         per_head = 8 // hkv                                # XCDs of a KV head share its tiles evenly
         assert (x, threads) == (8 * -(-tiles // per_head), 256), (hq, hkv, n_q)
