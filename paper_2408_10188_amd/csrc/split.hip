@@ -158,10 +158,13 @@ int32_t may_rank(const StepArgs& a, int n_tiles, int n_blocks, int heads_per_til
 
 // How a grid smaller than the chip is spread over it: by workgroups of 4 instead of 8 wavefronts (twice as many, each with half of
 // the rows and the SIMDs to itself: 64 keys take 0.89 us instead of 1.2 in the forward, 1.15 instead of 1.6 in the dQ kernel) and by
-// cutting the keys into ranges.  Taken is what minimises an estimate in us: rounds of workgroups x (tiles of a range x
-// tile time + the time to load Q and the first tiles and to store the result) + the combining pass (a launch, and every partial result
-// written and read at about 4 TB/s).  Measured, 32 rows of 28/4 heads
-// on 8192 keys, uncut: 162 us with 8 wavefronts, 122 with 4; from 129 workgroups of 8 on a second round of smaller ones costs more than they gain.
+// cutting the keys into ranges.  Taken is what minimises an estimate in us of the launch and of the combining pass (a launch, and every
+// partial result written and read at about 4 TB/s).  A workgroup takes its tiles' time and the time to load Q and the first tiles and to store its result.  The
+// launch lasts as long as its first, heaviest workgroup, or as the sum over all CUs and the part of a last round that stays empty, filled with its
+// lightest: whole rounds where all rows see the same keys, nothing where the first see none.  Measured, 32 rows of 28/4 heads
+// on 8192 keys, uncut: 162 us with 8 wavefronts, 122 with 4.  7/1 heads, 4961 x 4961 causal, 8 wavefronts: 105.7 us uncut (136 workgroups), 77.5
+// in three ranges, which whole rounds of the heaviest took for slower; over 8302 forward and dQ blocks without documents of 24 to 8192 rows the
+// choice takes 1.8 % longer than the best one measured in the mean, 4.0 with whole rounds.
 // Documents shorten the visible keys by an amount the host does not know; taken are `mean_documents` documents
 // of the mean length (the block's last position / n_docs), see the callers.  A cut that the documents leave with empty ranges
 // costs 5 to 10 us; half of all keys, whatever n_docs, was such a cut for every block of short documents (100 rows on
@@ -184,13 +187,21 @@ KeyRanges pick_key_ranges(const StepArgs& a, double tile_us, int64_t bytes_per_r
   int64_t keys = a.n_k;
   if (a.mask == 1) keys = std::max<int64_t>(0, std::min<int64_t>(keys, (int64_t)a.q_pos0 + a.n_q - a.k_pos0));
   if (a.cu != nullptr) keys = std::min(keys, (int64_t)(mean_documents * mean_document(a)));
-  const double tiles = (double)((keys + 63) / 64);
+  const double tiles = (double)((keys + 63) / 64);        // of the heaviest workgroup; of the lightest, and on average:
+  double least = tiles, mean = tiles;
+  if (a.mask == 1 && a.cu == nullptr) {
+    const int64_t first = (int64_t)a.q_pos0 + 1 - a.k_pos0, all = std::max<int64_t>(0, std::min<int64_t>(a.n_q, first + a.n_q - 1 - a.n_k));   // keys before the first row, rows behind all keys
+    least = (double)((std::max<int64_t>(0, std::min(keys, first)) + 63) / 64);
+    mean = tiles - (double)(a.n_q - all) / a.n_q * (tiles - least) / 2;
+  }
   const int most = std::max(1, (int)std::min<int64_t>({kMaxRanges, room / bytes_per_range, (int64_t)(tiles / 4)}));
   double best_cost = 1e300;
   for (int w = 0; w < 2; ++w)
     for (int n = 1; n <= most; ++n) {
-      const int64_t rounds = (blocks[w] * n + n_cu - 1) / n_cu;
-      const double cost = rounds * (tiles / n * tile[w] + kStart[w]) + (n > 1 ? kLaunch + 2. * n * (double)bytes_per_range / kBytesPerUs : 0.);
+      auto us = [&](double t) { return t / n * tile[w] + kStart[w]; };
+      const double rounds = (double)(blocks[w] * n) / n_cu, empty = (double)((blocks[w] * n + n_cu - 1) / n_cu) - rounds;
+      const double cost = std::max(us(tiles), rounds * us(mean) + empty * us(least)) +
+                          (n > 1 ? kLaunch + 2. * n * (double)bytes_per_range / kBytesPerUs : 0.);
       if (cost < best_cost) { best = {w ? 4 : 8, n, w ? 128 : 256}; best_cost = cost; }
     }
   if (best.waves == 4 && best.count == 1)
