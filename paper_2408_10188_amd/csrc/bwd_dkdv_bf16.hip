@@ -66,7 +66,7 @@ __device__ __forceinline__ void mfma32_v(f32x16& d, const u32x4& a, const u32x4&
 // kAdd: add to dk and dv (nsplit is 1; the reduction does it otherwise).
 template <bool kMask, bool kAdd>
 __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs a, BwdWorkspace w, int n_kt, int xcd_per_kv,
-                                                                       int nsplit) {
+                                                                       int nsplit, int rotate) {
   // LDS map: four Q tile slots in [0, 64 KiB), four dO tile slots in [64 KiB, 128 KiB), then the four
   // statistics slots.  Slots are selected at compile time (the loop is unrolled four tiles deep).
   // An LDS instruction's immediate offset reaches 64 KiB: reads of the upper regions go through
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void bwd_dkdv_bf16_kernel(StepArgs 
     kvh = blockIdx.x - item * a.Hkv;
   }
   int kt = item / nsplit;
-  const int split = item % nsplit;
+  const int split = (item - kt * nsplit + rotate * kt) % nsplit;
   const CuLocal cu = local_cu(a, reinterpret_cast<int32_t*>(lds + 8192), 64 * kWaves);
   if (kMask && worth_ranking(a, cu, a.k_pos0, a.k_pos0 + a.n_k - 1))
     kt = heaviest_first(kt, n_kt, 64 * kWaves, reinterpret_cast<int*>(lds), [&](int i) { return query_tiles_of_keys(a, cu, i * kKeys, kKeys); });
@@ -594,6 +594,19 @@ static int pick_shares(const StepArgs& a, int n_kt) {
   return best;
 }
 
+// Workgroups go to XCDs in turn, so that with an even number of shares an XCD of several that serve a KV head gets the same shares of every key
+// tile, with an odd one others from tile to tile.  The first way reads the Q and dO rows of a share into one L2 only, the second does not make
+// all its workgroups wait for the same rows at once, which counts while a share is short: 28/4 heads, 747 x 373, 16 shares 31.5 us, 17 27.9;
+// 4/2 heads, 2689 x 1344, 8 shares 39.5, 9 34.8.  Rotated by the tile's number an even number of short shares behaves as an odd one (28.6 and 35.3 us;
+// an odd number would behave as an even one).  From some 16 elements on both take the same time (7/1 heads, 4096 x 4096 causal, 8 shares of 56: 96.4 and 96.2), and
+// the first way reads less: 7/1 heads, 8192 x 8192 causal, 8 shares.
+static int rotate_shares(const StepArgs& a, int xcd_per_kv, int nsplit) {
+  if (xcd_per_kv < 2 || nsplit % 2 != 0) return 0;
+  double tiles = (double)tiles_of(a.n_q);
+  if (a.cu != nullptr) tiles = std::min(tiles, 2. * mean_document(a) / kBQ + 2.);
+  return tiles * a.group <= 16. * nsplit;
+}
+
 hipError_t launch_bwd_dkdv_bf16(const StepArgs& args, const BwdWorkspace& w, hipStream_t stream) {
   StepArgs a = args;
   const int n_kt = (a.n_k + kKeys - 1) / kKeys;
@@ -609,7 +622,7 @@ hipError_t launch_bwd_dkdv_bf16(const StepArgs& args, const BwdWorkspace& w, hip
   const bool add = a.accumulate && nsplit == 1;
   const auto kernel = no_mask ? (add ? bwd_dkdv_bf16_kernel<false, true> : bwd_dkdv_bf16_kernel<false, false>)
                               : (add ? bwd_dkdv_bf16_kernel<true, true> : bwd_dkdv_bf16_kernel<true, false>);
-  kernel<<<dim3(n_blocks), dim3(64 * kWaves), 0, stream>>>(a, w, n_kt, xcd_per_kv, nsplit);
+  kernel<<<dim3(n_blocks), dim3(64 * kWaves), 0, stream>>>(a, w, n_kt, xcd_per_kv, nsplit, rotate_shares(a, xcd_per_kv, nsplit));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || nsplit == 1) return e;
   const int64_t n4 = (int64_t)a.n_k * a.Hkv * 32;

@@ -1,7 +1,7 @@
 // Backward ring step, dQ kernel (query-stationary) on bf16 matrix cores, head_dim 128.
 //
 // Same skeleton as the forward kernel: the query rows of the heads that share a KV head are one list of (row, head)
-// pairs, a workgroup owns kWaves * 32 of them, a wavefront 32: their Q and dO (MFMA
+// pairs, a workgroup owns up to kWaves * 32 of them, a wavefront 32: their Q and dO (MFMA
 // B operands), the dQ^T accumulator (128 d x 32 rows) and the two row statistics (-LSE*log2e,
 // delta) stay in registers for the whole call.  64-key tiles of K and V stream through two four-slot
 // LDS rings filled by asynchronous global->LDS copies straight from the caller's tensors (natural

@@ -1,7 +1,7 @@
 // Forward ring step on bf16 matrix cores, head_dim 128.
 //
 // The query rows of the heads that share a KV head are one list of (row, head) pairs, head fastest: row i of the
-// list is query row i / group of head i % group.  A workgroup owns kWaves * 32 rows of the list, a wavefront
+// list is query row i / group of head i % group.  A workgroup owns up to kWaves * 32 rows of the list, a wavefront
 // 32: their Q (MFMA B operands, 32 VGPRs), the O^T accumulator (128 d x 32 rows, 64 VGPRs) and the softmax statistics stay
 // in registers for the whole call.  K and V tiles of 64 keys stream through two four-slot LDS rings
 // filled by asynchronous global->LDS copies straight from the caller's tensors (one natural-orientation

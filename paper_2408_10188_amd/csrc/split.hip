@@ -1,7 +1,7 @@
 // Cutting the key range of query-stationary kernels (forward, dQ) into several workgroups per query tile,
 // and the kernels that combine the partial results.
 //
-// A workgroup owns 256 or 128 (row, head) pairs of one KV head and takes a CU for as long as it needs for all its keys, so a
+// A workgroup owns up to 256 or 128 (row, head) pairs of one KV head and takes a CU for as long as it needs for all its keys, so a
 // block of few rows leaves most of the chip idle: 203 rows x 28 / 4 heads are 24 workgroups of 256 on 256 CUs, 783 us for 32768
 // keys with the final cast.  With the keys cut in ranges, each storing its partial result in the caller's workspace, the same
 // two calls take 107 us.
