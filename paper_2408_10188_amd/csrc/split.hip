@@ -162,9 +162,11 @@ int32_t may_rank(const StepArgs& a, int n_tiles, int n_blocks, int heads_per_til
 // partial result written and read at about 4 TB/s).  A workgroup takes its tiles' time and the time to load Q and the first tiles and to store its result.  The
 // launch lasts as long as its first, heaviest workgroup, or as the sum over all CUs and the part of a last round that stays empty, filled with its
 // lightest: whole rounds where all rows see the same keys, nothing where the first see none.  Measured, 32 rows of 28/4 heads
-// on 8192 keys, uncut: 162 us with 8 wavefronts, 122 with 4.  7/1 heads, 4961 x 4961 causal, 8 wavefronts: 105.7 us uncut (136 workgroups), 77.5
+// on 8192 keys, uncut: 162 us with 8 wavefronts, 122 with 4.  7/1 heads, 4961 x 4961 causal, 8 wavefronts: 103.8 us uncut (136 workgroups), 73.3
 // in three ranges, which whole rounds of the heaviest took for slower; over 8302 forward and dQ blocks without documents of 24 to 8192 rows the
 // choice takes 1.8 % longer than the best one measured in the mean, 4.0 with whole rounds.
+// With a few documents the same holds (7/1 heads, 5651 x 5651, documents of 5000 and 651: 117.9 us uncut, 82.4 in three ranges; of 6457 forward blocks 508 are more than 3 %
+// faster for it, 36 slower); many end one another's tiles at random, and a cut between short ones costs (8/8 heads, 5553 x 5553, 28 documents, dQ: 27 and 35 us).
 // Documents shorten the visible keys by an amount the host does not know; taken are `mean_documents` documents
 // of the mean length (the block's last position / n_docs), see the callers.  A cut that the documents leave with empty ranges
 // costs 5 to 10 us; half of all keys, whatever n_docs, was such a cut for every block of short documents (100 rows on
@@ -189,7 +191,7 @@ KeyRanges pick_key_ranges(const StepArgs& a, double tile_us, int64_t bytes_per_r
   if (a.cu != nullptr) keys = std::min(keys, (int64_t)(mean_documents * mean_document(a)));
   const double tiles = (double)((keys + 63) / 64);        // of the heaviest workgroup; of the lightest, and on average:
   double least = tiles, mean = tiles;
-  if (a.mask == 1 && a.cu == nullptr) {
+  if (a.mask == 1 && (a.cu == nullptr || a.n_docs <= 8)) {
     const int64_t first = (int64_t)a.q_pos0 + 1 - a.k_pos0, all = std::max<int64_t>(0, std::min<int64_t>(a.n_q, first + a.n_q - 1 - a.n_k));   // keys before the first row, rows behind all keys
     least = (double)((std::max<int64_t>(0, std::min(keys, first)) + 63) / 64);
     mean = tiles - (double)(a.n_q - all) / a.n_q * (tiles - least) / 2;
