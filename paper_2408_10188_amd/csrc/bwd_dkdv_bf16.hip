@@ -550,15 +550,15 @@ static double dkdv_us(const TileWork& w, int n_kv_heads, int n, int n_cu) {
 // tile sees; of several it knows only how many there are, and one long document wants another count than many of the mean length.
 // So the count that gives every CU one workgroup (two where tiles differ), at most eight, is left only for one that the estimate finds
 // faster, by 3 %, or with several documents by 10 % both if one of them holds everything and if the longest is twice the mean.
-// Measured with every count up to 32: 1276 blocks without documents (8 arrangements of heads, 50 to 4000 rows on 50 to 34000 keys, with
-// and without a causal mask) take 1.0 % longer than with their best count in the mean, 247 blocks of packs as synth.py draws
-// them 2.5 %; 375 with made-up documents (clips, halves, one long first or last, few rows behind many keys) 3.5 %, where the
-// count that fills the CUs takes 20 % and a rule that trusts the mean length up to three times as long.  us by count:
-//   28/4 heads, 760 x 1520:               1: 152  2: 91  3: 68  4: 51  5: 47  6: 73 (288 workgroups)
+// Measured with every count up to 32: 4434 blocks without documents (5 arrangements of heads, 40 to 5000 rows on 40 to 17000 keys, with
+// and without a causal mask) take 1.2 % longer than with their best count in the mean, 62 blocks of packs as synth.py draws
+// them 2.9 %; 1265 with made-up documents (clips of 60 to 300 tokens, longer ones, one long first or last, few rows behind many keys) 6 %, where
+// a rule that trusts the mean length takes 14 % and up to 2.9 times as long.  us by count:
+//   28/4 heads, 760 x 1520:               1: 117  2: 73  3: 56  4: 52  5: 49  6: 68 (288 workgroups)
 //   8/8 heads, 320 x 640:                 1: 17  2: 21  4: 25  6: 28
-//   28/4 heads, 1000 rows behind 3000:    1: 158  2: 111  3: 142  4: 123 (nearly all tiles see all rows: whole rounds)
-//   7/1 heads, 2500 x 2500 causal:        1: 361  4: 104  8: 65  16: 49  24: 54
-//   4/2 heads, 4000 x 4000, documents:    one long 1: 221  2: 124  4: 80  8: 76;  clips of 60 to 300 1: 30  2: 30  4: 38  8: 48
+//   28/4 heads, 1000 rows behind 3000:    1: 163  2: 113  3: 141  4: 125 (nearly all tiles see all rows: whole rounds)
+//   7/1 heads, 2500 x 2500 causal:        1: 357  4: 108  8: 68  16: 51  24: 57
+//   4/2 heads, 4000 x 4000, documents:    one long 1: 221  2: 124  4: 79  8: 72;  clips of 60 to 300 1: 35  2: 33  4: 31  8: 49
 static int pick_shares(const StepArgs& a, int n_kt) {
   const int base = n_kt * a.Hkv, q_tiles = (int)tiles_of(a.n_q), n_cu = cu_count();
   const int limit = (int)std::min<int64_t>({kSplitMaxRanges, kSplitMaxBlocks / base, (int64_t)q_tiles * a.group});
