@@ -235,9 +235,9 @@ def ulysses_backward(shape, T, q, k, v, cu_seqlens, n_docs, o_final, d_o, lse, d
     With cu_host (host copy of cu_seqlens) and q_block the step is cut into query blocks of
     q_block rows, launched one after the other: the workgroups of a launch then walk the same
     Q / dO rows (dK/dV kernel) at the same time and share them in L2, where one launch over a
-    long document lets them drift apart and re-read the operands (measured: an order of
-    magnitude less HBM traffic, but no shorter, because every block's launch ends in a partly
-    filled round of workgroups).  dk / dv rows are overwritten by the first block that reaches
+    long document lets them drift apart and re-read the operands (256K packed tokens, 7/1 heads, blocks of
+    8192: 13 GB read by dK/dV instead of 45 to 52, but 96.4 ms a pass instead of 93.6, because every block's launch
+    ends in a partly filled round of workgroups).  dk / dv rows are overwritten by the first block that reaches
     them and added to by later ones.
     With `side` the dK/dV kernels run on the current torch stream and the dQ kernels on side.stream."""
     import torch
